@@ -14,10 +14,24 @@
 #include "ufp4_device.h"
 #include "ufp4_internal.h"
 
+#include <math.h>
+
 namespace ufp4 {
 
-constexpr int BM = 128, BN = 128;
-static_assert(BM == kPanelRows && BN == kPanelRows, "a dense tile is one operand panel");
+// Tile configuration of gemm_f32_kernel: WM x WN x WK waves. A wave owns WTM x WTN MFMA tiles of 32 x 32 outputs, its
+// row (column) tiles WM (WN) tiles apart; the WK wave groups split every stage's K-blocks between them and add their
+// partial sums through LDS at the end. A stage holds SKB blocks per group.
+template <int WTM_, int WTN_, int WM_, int WN_, int WK_, int SKB_>
+struct TileCfg {
+    static constexpr int WTM = WTM_, WTN = WTN_, WM = WM_, WN = WN_, WK = WK_, SKB = SKB_;
+    static constexpr int BM = 32 * WTM * WM, BN = 32 * WTN * WN;
+    static constexpr int kWaves = WM * WN * WK, kThreads = 64 * kWaves;
+    static constexpr int kStageBlocks = SKB * WK;
+    // staging units (64 rows of one block) of A and B in a stage, dealt round robin to the waves
+    static constexpr int kUnitsA = kStageBlocks * BM / 64, kUnitsB = kStageBlocks * BN / 64;
+    static_assert(BM % 64 == 0 && BN % 64 == 0, "a staging unit lies in one operand");
+    static_assert(kUnitsA == kWaves && kUnitsB <= kWaves, "one unit of A and at most one of B per wave and stage");
+};
 
 // Offsets of (row, block) in the panel layout, the row counted from a tile's first row (row0 within its panel).
 __device__ __forceinline__ int64_t code_off(int row0, int row, int64_t kb, int64_t pld) {
@@ -50,6 +64,7 @@ struct Tile {
 
 // Ragged-M: find the group owning global m-tile t. Wave 0 runs a prefix sum over per-group tile counts,
 // 64 groups at a time; the result goes through LDS. Returns false for tiles past the last group.
+template <int BM>
 __device__ bool resolve_ragged_m(const GemmJob& j, int32_t* grp, int64_t t, int& g_out, int64_t& local_tile) {
     const int tid = threadIdx.x;
     if (tid == 0) grp[0] = -1;
@@ -60,6 +75,7 @@ __device__ bool resolve_ragged_m(const GemmJob& j, int32_t* grp, int64_t t, int&
             const int g = g0 + tid;
             int64_t cnt = 0;
             if (g < j.G) cnt = (j.offsets[g + 1] - j.offsets[g] + BM - 1) / BM;
+            if (cnt < 0) cnt = 0;  // offsets that decrease: an empty group
             int64_t incl = cnt;
 #pragma unroll
             for (int d = 1; d < 64; d <<= 1) {
@@ -125,12 +141,13 @@ __device__ int64_t padded_start(const int64_t* off, int g, int64_t* slot) {
 
 // Resolve the workgroup's output tile (dense, ragged-M group or ragged-K group). Returns false when the
 // workgroup has nothing to do (a ragged-M tile index past the last group); all threads agree.
+template <int BM, int BN>
 __device__ bool resolve_tile(const GemmJob& j, int32_t* grp, int64_t* pad, const TilePos& pos, Tile& tl) {
     const int64_t tn = pos.tn;
     if (j.mode == kGemmRaggedM) {
         int g;
         int64_t lt;
-        if (!resolve_ragged_m(j, grp, pos.tm, g, lt)) return false;
+        if (!resolve_ragged_m<BM>(j, grp, pos.tm, g, lt)) return false;
         const int64_t r0 = j.offsets[g] + lt * BM;
         const int64_t end = j.offsets[g + 1] < j.M ? j.offsets[g + 1] : j.M;  // offsets past M_total: ignored
         const int64_t rows_g = end - r0;
@@ -164,12 +181,14 @@ __device__ bool resolve_tile(const GemmJob& j, int32_t* grp, int64_t* pad, const
             tl.nkb = p1 > p0 ? (p1 - p0) / 16 : 0;
             c_base = (int64_t)g * j.M * j.ldc;
         }
-        // BM = BN = 128: dense tiles are whole panels
-        tl.a = j.a + tm * j.a_pld + kb0 * kPanelBlockBytes;
-        tl.as = j.as + tm * j.as_pld + kb0 * kPanelBlockScales;
-        tl.b = j.b + tn * j.b_pld + kb0 * kPanelBlockBytes;
-        tl.bs = j.bs + tn * j.bs_pld + kb0 * kPanelBlockScales;
-        tl.a_row0 = tl.b_row0 = 0;
+        // BM and BN divide the panel's 128 rows: a tile lies in one panel
+        const int64_t pa = tm * BM / kPanelRows, pb = tn * BN / kPanelRows;
+        tl.a = j.a + pa * j.a_pld + kb0 * kPanelBlockBytes;
+        tl.as = j.as + pa * j.as_pld + kb0 * kPanelBlockScales;
+        tl.b = j.b + pb * j.b_pld + kb0 * kPanelBlockBytes;
+        tl.bs = j.bs + pb * j.bs_pld + kb0 * kPanelBlockScales;
+        tl.a_row0 = (int)(tm * BM % kPanelRows);
+        tl.b_row0 = (int)(tn * BN % kPanelRows);
         const int64_t mr = j.M - tm * BM, nr = j.N - tn * BN;
         tl.mrows = (int)(mr < BM ? mr : BM);
         tl.nrows = (int)(nr < BN ? nr : BN);
@@ -201,8 +220,6 @@ __device__ bool resolve_tile(const GemmJob& j, int32_t* grp, int64_t* pad, const
 typedef float v16f __attribute__((ext_vector_type(16)));
 typedef short v4s __attribute__((ext_vector_type(4)));
 
-constexpr int SKB2 = 4;       // K-blocks per LDS stage
-constexpr int PL2 = BM + 1;   // 8-byte entries per LDS plane (one plane per block and half-wave)
 
 // 8 uniform codes (one packed dword of sign-magnitude nibbles) -> 8 fp8 e4m3 bytes. The byte s000 0mmm is an
 // e4m3 subnormal worth (-1)^s * m * 2^-9, so the code k becomes k * 2^-9 exactly (the product of two codes
@@ -254,13 +271,22 @@ __device__ __forceinline__ ScaleOp scale_op_b(float s) {
     return {make_uint2(q01, bf16_pair(p2, p0)), make_uint2(bf16_pair(p1, p2), q01)};
 }
 
-struct alignas(16) GemmSmem2 {
-    // plane (block * 2 + half) holds one 8-byte entry per row: codes (8 e4m3 bytes) and outer-product scale
-    // operands
-    uint2 a[2][SKB2 * 2 * PL2];
-    uint2 b[2][SKB2 * 2 * PL2];
-    uint2 as[2][SKB2 * 2 * PL2];
-    uint2 bs[2][SKB2 * 2 * PL2];
+template <class C>
+struct alignas(16) GemmStageSmem {
+    // plane (block * 2 + half) holds one 8-byte entry per row: codes (8 e4m3 bytes) and outer-product scale operands
+    uint2 a[2][C::kStageBlocks * 2][C::BM];
+    uint2 b[2][C::kStageBlocks * 2][C::BN];
+    uint2 as[2][C::kStageBlocks * 2][C::BM];
+    uint2 bs[2][C::kStageBlocks * 2][C::BN];
+};
+template <class C>
+struct GemmSmem {
+    union {
+        GemmStageSmem<C> st;
+        // partial sums exchanged between the two wave groups: [group][wave of the group][half of the wave's
+        // accumulators][lane]
+        float part[C::WK > 1 ? 2 : 1][C::WM * C::WN][8 * C::WTM * C::WTN][64];
+    };
     int32_t grp[2];
     int64_t pad;
 };
@@ -295,25 +321,24 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, ui
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, (int)bytes, 0x00020000);
 }
 
-// Registers of one stage held by one thread: two blocks of codes of one row, and their two scales.
-struct StageRegs {
-    uint2 c0, c1;
-    uint32_t s0, s1;
+// One staging unit held by one lane: the codes and the scale of one (row, block).
+struct Unit {
+    uint2 c;
+    uint32_t s;
 };
 
-// Work split: 8 waves per 128 x 128 tile; wave (wm, wn) owns rows 64 wm .. +64 and columns 32 wn .. +32, i.e.
-// two 32 x 32 MFMA tiles. At <= 128 VGPRs two workgroups share a CU (four waves per SIMD), which is what
-// lets MFMAs and VALU FMAs of different waves overlap: a single wave issues neither back to back.
-constexpr int kWaves2 = 8;
-
-template <int FMT, int OUT>
-__global__ __launch_bounds__(512, 2) void gemm_f32_kernel(GemmArgs args) {
-    __shared__ GemmSmem2 sm;
+// Work split (Tile128): 8 waves per 128 x 128 tile; wave (wm, wn) owns two 32 x 32 MFMA tiles. At <= 128 VGPRs two
+// workgroups share a CU (four waves per SIMD), which is what lets MFMAs and VALU FMAs of different waves overlap: a
+// single wave issues neither back to back.
+template <int FMT, int OUT, class C>
+__global__ __launch_bounds__(C::kThreads, 4) void gemm_f32_kernel(GemmArgs args) {
+    __shared__ GemmSmem<C> sm;
     const GemmJob& j = args.j;
     const int tid = threadIdx.x;
+    constexpr int BM = C::BM, BN = C::BN;
 
     Tile tl;
-    if (!resolve_tile(j, sm.grp, &sm.pad, grid_pos(), tl)) return;
+    if (!resolve_tile<BM, BN>(j, sm.grp, &sm.pad, grid_pos(), tl)) return;
     // the buffer resources below must live in SGPRs
     tl.a = uniform_ptr(tl.a);
     tl.b = uniform_ptr(tl.b);
@@ -323,154 +348,439 @@ __global__ __launch_bounds__(512, 2) void gemm_f32_kernel(GemmArgs args) {
     tl.b_row0 = __builtin_amdgcn_readfirstlane(tl.b_row0);
     tl.mrows = __builtin_amdgcn_readfirstlane(tl.mrows);
     tl.nrows = __builtin_amdgcn_readfirstlane(tl.nrows);
-    tl.nkb = uniform_i64(tl.nkb);
-
-    const int lane = tid & 63, h = lane >> 5, l32 = lane & 31;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave >> 2, wn = wave & 3;
-
-    float acc[2][16];
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) acc[a][i] = 0.0f;
-
     // 32-bit stage counters keep the loop (and the buffer loads' stage offsets) on the scalar unit
     const int nkb = __builtin_amdgcn_readfirstlane((int)tl.nkb);
-    const int nstages = (nkb + SKB2 - 1) / SKB2;
+    const int nstages = (nkb + C::kStageBlocks - 1) / C::kStageBlocks;
 
-    // Staging: waves 0-3 fetch A, waves 4-7 B; thread (row, pair) takes blocks 2 pair and 2 pair + 1 of its
-    // row in every stage (2 x 8 bytes of codes and 2 scales). A wave covers 64 consecutive rows of one block,
-    // i.e. contiguous runs of the panel layout.
-    const bool st_a = wave < 4;
-    const int srow = tid & 127, spair = (tid >> 7) & 1;
-    const int rows = st_a ? tl.mrows : tl.nrows;
-    const int row0 = st_a ? tl.a_row0 : tl.b_row0;
-    const int64_t cpld = st_a ? j.a_pld : j.b_pld;   // bytes
-    const int64_t spld = st_a ? j.as_pld : j.bs_pld;  // floats
-    // the resources end at the last valid byte of the tile: loads of rows past it, or of blocks past the end
-    // in the last panel, read zeros
-    const int64_t last_panel = (row0 + rows - 1) / kPanelRows;
-    const __amdgpu_buffer_rsrc_t rc = make_rsrc(st_a ? (const void*)tl.a : (const void*)tl.b,
-                                                (uint32_t)(last_panel * cpld + (int64_t)nkb * kPanelBlockBytes));
-    const __amdgpu_buffer_rsrc_t rs =
-        make_rsrc(st_a ? (const void*)tl.as : (const void*)tl.bs,
-                  (uint32_t)((last_panel * spld + (int64_t)nkb * kPanelBlockScales) * 4));
-    const int voc = (int)code_off(row0, srow, 2 * spair, cpld);
-    const int vos = (int)scale_off(row0, srow, 2 * spair, spld) * 4;
+    const int lane = tid & 63, h = lane >> 5, l32 = lane & 31;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wk = wave / (C::WM * C::WN), wt = wave % (C::WM * C::WN);  // K group, tile of the wave
+    const int wm = wt / C::WN, wn = wt % C::WN;
+    // a wave whose outputs all lie past the problem's edge only helps staging
+    const bool live = wm * 32 < tl.mrows && wn * 32 < tl.nrows;
 
-    auto load = [&](StageRegs& r, int s) {
-        const int soc = __builtin_amdgcn_readfirstlane(s * SKB2 * (int)kPanelBlockBytes);
-        const int sos = __builtin_amdgcn_readfirstlane(s * SKB2 * (int)kPanelBlockScales * 4);
-        r.c0 = __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(rc, voc, soc, 0));
-        r.c1 = __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(rc, voc + (int)kPanelBlockBytes, soc, 0));
-        r.s0 = __builtin_amdgcn_raw_buffer_load_b32(rs, vos, sos, 0);
-        r.s1 = __builtin_amdgcn_raw_buffer_load_b32(rs, vos + (int)kPanelBlockScales * 4, sos, 0);
+    float acc[C::WTM][C::WTN][16];
+#pragma unroll
+    for (int a = 0; a < C::WTM; ++a)
+#pragma unroll
+        for (int b = 0; b < C::WTN; ++b)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[a][b][i] = 0.0f;
+
+    // Staging: in every stage wave w fetches unit w of A and (w < kUnitsB) unit w of B, a unit being 64 rows of one
+    // block, i.e. contiguous runs of the panel layout. The resources end at the last valid byte of the tile, and a
+    // block past the reduction gets an empty one: rows past the tile's last panel and blocks past the end read zeros.
+    const int arow = (wave % (BM / 64)) * 64 + lane, ablk = wave / (BM / 64);
+    const int brow = (wave % (BN / 64)) * 64 + lane, bblk = wave / (BN / 64);
+    const bool has_b = C::kUnitsB == C::kWaves || wave < C::kUnitsB;
+    const int64_t a_last = (tl.a_row0 + tl.mrows - 1) / kPanelRows, b_last = (tl.b_row0 + tl.nrows - 1) / kPanelRows;
+    const int a_cbytes = (int)(a_last * j.a_pld + (int64_t)nkb * kPanelBlockBytes);
+    const int a_sbytes = (int)((a_last * j.as_pld + (int64_t)nkb * kPanelBlockScales) * 4);
+    const int b_cbytes = (int)(b_last * j.b_pld + (int64_t)nkb * kPanelBlockBytes);
+    const int b_sbytes = (int)((b_last * j.bs_pld + (int64_t)nkb * kPanelBlockScales) * 4);
+    const int voca = (int)code_off(tl.a_row0, arow, ablk, j.a_pld), vosa = (int)scale_off(tl.a_row0, arow, ablk, j.as_pld) * 4;
+    const int vocb = (int)code_off(tl.b_row0, brow, bblk, j.b_pld), vosb = (int)scale_off(tl.b_row0, brow, bblk, j.bs_pld) * 4;
+
+    auto fetch = [&](Unit& u, const uint8_t* cb, const float* sb, int cbytes, int sbytes, int voc, int vos, int blk, int s) {
+        const int b0 = s * C::kStageBlocks;
+        const bool in = b0 + blk < nkb;
+        const int soc = __builtin_amdgcn_readfirstlane(b0 * (int)kPanelBlockBytes);
+        const int sos = __builtin_amdgcn_readfirstlane(b0 * (int)kPanelBlockScales * 4);
+        u.c = __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(make_rsrc(cb, in ? cbytes : 0), voc, soc, 0));
+        u.s = __builtin_amdgcn_raw_buffer_load_b32(make_rsrc(sb, in ? sbytes : 0), vos, sos, 0);
+    };
+    auto load = [&](Unit& a, Unit& b, int s) {
+        fetch(a, tl.a, tl.as, a_cbytes, a_sbytes, voca, vosa, ablk, s);
+        if (has_b) fetch(b, tl.b, tl.bs, b_cbytes, b_sbytes, vocb, vosb, bblk, s);
     };
     auto conv = [](uint32_t d) -> uint2 {
         if constexpr (FMT == kFmtUniform) return uniform_to_e4m3(d);
         else return e2m1_to_e4m3(d);
     };
-    auto put = [&](int buf, const StageRegs& r) {
-        uint2* cp = st_a ? sm.a[buf] : sm.b[buf];
-        uint2* sp = st_a ? sm.as[buf] : sm.bs[buf];
-        const int e0 = (4 * spair) * PL2 + srow;  // plane (2 pair, half 0)
-        cp[e0] = conv(r.c0.x);
-        cp[e0 + PL2] = conv(r.c0.y);
-        cp[e0 + 2 * PL2] = conv(r.c1.x);
-        cp[e0 + 3 * PL2] = conv(r.c1.y);
-        const ScaleOp o0 = st_a ? scale_op_a(__uint_as_float(r.s0)) : scale_op_b(__uint_as_float(r.s0));
-        const ScaleOp o1 = st_a ? scale_op_a(__uint_as_float(r.s1)) : scale_op_b(__uint_as_float(r.s1));
-        sp[e0] = o0.h0;
-        sp[e0 + PL2] = o0.h1;
-        sp[e0 + 2 * PL2] = o1.h0;
-        sp[e0 + 3 * PL2] = o1.h1;
+    auto put_a = [&](int buf, const Unit& u) {
+        sm.st.a[buf][2 * ablk][arow] = conv(u.c.x);
+        sm.st.a[buf][2 * ablk + 1][arow] = conv(u.c.y);
+        const ScaleOp o = scale_op_a(__uint_as_float(u.s));
+        sm.st.as[buf][2 * ablk][arow] = o.h0;
+        sm.st.as[buf][2 * ablk + 1][arow] = o.h1;
     };
-    auto compute = [&](int buf, int s) {
-        const int left = nkb - s * SKB2;
-        const int kbn = left < SKB2 ? left : SKB2;
+    auto put_b = [&](int buf, const Unit& u) {
+        if (!has_b) return;
+        sm.st.b[buf][2 * bblk][brow] = conv(u.c.x);
+        sm.st.b[buf][2 * bblk + 1][brow] = conv(u.c.y);
+        const ScaleOp o = scale_op_b(__uint_as_float(u.s));
+        sm.st.bs[buf][2 * bblk][brow] = o.h0;
+        sm.st.bs[buf][2 * bblk + 1][brow] = o.h1;
+    };
+    auto block = [&](int buf, int kb) {
+        const int pl = (C::SKB * wk + kb) * 2 + h;
 #pragma unroll
-        for (int kb = 0; kb < SKB2; ++kb) {
-            if (kb < kbn) {
-                const int pl = (kb * 2 + h) * PL2;
-                const uint2 bc = sm.b[buf][pl + wn * 32 + l32];
-                const uint2 bw = sm.bs[buf][pl + wn * 32 + l32];
+        for (int b = 0; b < C::WTN; ++b) {
+            const int col = (b * C::WN + wn) * 32 + l32;
+            const uint2 bc = sm.st.b[buf][pl][col], bw = sm.st.bs[buf][pl][col];
 #pragma unroll
-                for (int a = 0; a < 2; ++a) {
-                    const int ra = pl + wm * 64 + a * 32 + l32;
-                    const v16f d = block_dot(sm.a[buf][ra], bc);
-                    const v16f w = scale_outer(sm.as[buf][ra], bw);
+            for (int a = 0; a < C::WTM; ++a) {
+                const int row = (a * C::WM + wm) * 32 + l32;
+                const v16f d = block_dot(sm.st.a[buf][pl][row], bc);
+                const v16f w = scale_outer(sm.st.as[buf][pl][row], bw);
 #pragma unroll
-                    for (int i = 0; i < 16; ++i) acc[a][i] = __builtin_fmaf(d[i], w[i], acc[a][i]);
-                }
+                for (int i = 0; i < 16; ++i) acc[a][b][i] = __builtin_fmaf(d[i], w[i], acc[a][b][i]);
             }
         }
     };
+    // a full stage from LDS buffer `buf`, and the next stage's units (fetched one stage earlier) into the other buffer
+    auto stage = [&](int buf, const Unit& na, const Unit& nb) {
+        if (live) {
+#pragma unroll
+            for (int kb = 0; kb < C::SKB; ++kb) {
+                block(buf, kb);
+                if (kb == C::SKB / 2 - 1) put_a(buf ^ 1, na);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            put_b(buf ^ 1, nb);
+        } else {
+            put_a(buf ^ 1, na);
+            put_b(buf ^ 1, nb);
+        }
+    };
 
-    if (nstages > 0) {
-        // Loads are issued unconditionally (past the last stage they read zeros or unused bytes) so that the
-        // wait before each LDS write counts exactly the four loads of the stage fetched after it.
-        StageRegs r0, r1;
-        load(r0, 0);
-        load(r1, 1);
-        put(0, r0);
+    if (nkb > 0) {
+        const int nfull = nkb / C::kStageBlocks;
+        Unit a0, b0, a1, b1;
+        load(a0, b0, 0);
+        load(a1, b1, 1);
+        put_a(0, a0);
+        put_b(0, b0);
         __syncthreads();
-        // stage s computes from LDS buffer s % 2 while stage s + 2 is fetched into the registers that held
-        // stage s and stage s + 1 (fetched one stage earlier) is written to the other buffer
-        for (int s = 0; s < nstages; s += 2) {
-            load(r0, s + 2);
-            compute(0, s);
-            if (s + 1 >= nstages) break;
-            put(1, r1);
+        // stage s computes from LDS buffer s % 2 while stage s + 2 is fetched into the registers that held stage s and
+        // stage s + 1 (fetched one stage earlier) is written to the other buffer; past the end zeros are fetched
+        for (int s = 0; s < nfull; s += 2) {
+            load(a0, b0, s + 2);
+            stage(0, a1, b1);
             __syncthreads();
-            load(r1, s + 3);
-            compute(1, s + 1);
-            if (s + 2 >= nstages) break;
-            put(0, r0);
+            if (s + 1 >= nfull) break;
+            load(a1, b1, s + 3);
+            stage(1, a0, b0);
             __syncthreads();
+        }
+        // the blocks of a partial last stage
+        if (live) {
+#pragma unroll 1
+            for (int kb = 0; kb < nkb - nfull * C::kStageBlocks - C::SKB * wk && kb < C::SKB; ++kb) block(nfull & 1, kb);
         }
     }
 
     // uniform: the fp8 subnormal encoding scaled every product by 2^-18
     const float mul = FMT == kFmtUniform ? 262144.0f : 1.0f;
+    auto store = [&](int a, int b, int i, float sum) {
+        const int row = (a * C::WM + wm) * 32 + 8 * (i >> 2) + 4 * h + (i & 3), col = (b * C::WN + wn) * 32 + l32;
+        if (row >= tl.mrows || col >= tl.nrows) return;
+        const float v = sum * mul;
+        const int64_t off = tl.c_off + (int64_t)row * j.ldc + col;
+        if constexpr (OUT == kOutF32) {
+            static_cast<float*>(j.c)[off] = v;
+        } else {
+            static_cast<uint16_t*>(j.c)[off] = __builtin_bit_cast(uint16_t, (__bf16)v);  // RNE
+        }
+    };
+    if constexpr (C::WK == 1) {
 #pragma unroll
-    for (int a = 0; a < 2; ++a) {
-        const int col = wn * 32 + l32;
-        if (col >= tl.nrows) continue;
+        for (int a = 0; a < C::WTM; ++a)
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const int row = wm * 64 + a * 32 + 8 * (i >> 2) + 4 * h + (i & 3);
-            if (row >= tl.mrows) continue;
-            const float v = acc[a][i] * mul;
-            const int64_t off = tl.c_off + (int64_t)row * j.ldc + col;
-            if constexpr (OUT == kOutF32) {
-                static_cast<float*>(j.c)[off] = v;
-            } else {
-                static_cast<uint16_t*>(j.c)[off] = __builtin_bit_cast(uint16_t, (__bf16)v);  // RNE
+            for (int b = 0; b < C::WTN; ++b)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) store(a, b, i, acc[a][b][i]);
+    } else {
+        static_assert(C::WK == 2, "two K groups");
+        // each group hands the other half of its accumulators over and finishes (adds and stores) its own half
+        __syncthreads();  // the last stage's LDS accesses
+        float(*const mine)[64] = sm.part[wk][wt];
+        float(*const other)[64] = sm.part[1 - wk][wt];
+#pragma unroll
+        for (int a = 0; a < C::WTM; ++a)
+#pragma unroll
+            for (int b = 0; b < C::WTN; ++b)
+#pragma unroll
+                for (int i = 0; i < 8; ++i)
+                    mine[8 * (a * C::WTN + b) + i][lane] = wk ? acc[a][b][i] : acc[a][b][8 + i];
+        __syncthreads();
+#pragma unroll
+        for (int a = 0; a < C::WTM; ++a)
+#pragma unroll
+            for (int b = 0; b < C::WTN; ++b)
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    const float t = other[8 * (a * C::WTN + b) + i][lane];  // sums in the order group 0 + group 1
+                    if (wk) store(a, b, 8 + i, t + acc[a][b][8 + i]);
+                    else store(a, b, i, acc[a][b][i] + t);
+                }
+    }
+}
+
+using Tile128 = TileCfg<2, 1, 2, 4, 1, 4>;      // 128 x 128, 8 waves
+using Tile128K2 = TileCfg<2, 1, 2, 4, 2, 4>;    // 128 x 128, 16 waves in two K groups
+using Tile128x64 = TileCfg<1, 1, 4, 2, 1, 4>;   // 128 x 64, 8 waves
+
+static dim3 gemm_grid(const GemmJob& j, int bm, int bn) {
+    dim3 grid((unsigned)((j.N + bn - 1) / bn), (unsigned)((j.M + bm - 1) / bm), 1);
+    if (j.mode == kGemmRaggedM) grid.y += (unsigned)j.G;  // each group may end in a partial tile
+    else if (j.mode == kGemmRaggedK) grid.z = (unsigned)j.G;
+    return grid;
+}
+
+template <int FMT, int OUT, class C>
+static hipError_t launch_t(const GemmJob& j, hipStream_t s) {
+    const dim3 grid = gemm_grid(j, C::BM, C::BN);
+    if (grid.x == 0 || grid.y == 0 || grid.z == 0) return hipSuccess;
+    GemmArgs args{j};
+    gemm_f32_kernel<FMT, OUT, C><<<grid, C::kThreads, 0, s>>>(args);
+    return hipGetLastError();
+}
+
+// ------------------------------------------------------------------------------------------------
+// Problems too small to fill the chip with the kernel above. A workgroup owns one (32 WTM) x (32 WTN) output tile and
+// splits its reduction over NW waves; every wave loads its own operand fragments straight from global memory into
+// registers (no LDS staging, so no barrier until the partial sums are added through LDS).
+// ------------------------------------------------------------------------------------------------
+template <int WTM_, int WTN_, int NW_, int U_, int EU_>
+struct DirectCfg {
+    static constexpr int WTM = WTM_, WTN = WTN_, NW = NW_;
+    static constexpr int BM = 32 * WTM, BN = 32 * WTN, kThreads = 64 * NW;
+    static constexpr int U = U_;    // blocks per group: one group is computed while the next is fetched
+    static constexpr int EU = EU_;  // waves per SIMD the registers are bounded for
+    // the partial sums pass through LDS in kPasses slices of kSlice accumulators per wave (32 KB)
+    static constexpr int kAcc = 16 * WTM * WTN, kSlice = kAcc < 128 / NW ? kAcc : 128 / NW, kPasses = kAcc / kSlice;
+    static_assert(kAcc % kSlice == 0 && kSlice % NW == 0, "slices are shared evenly");
+};
+
+// Outer-product operands of a lane's own half, from its row's scale. K slots 0-3 (lanes 0-31) and 4-7 (lanes 32-63):
+//   A: a0 a1 a0 a1 | a0 a1 a2 a2        B: b0 b0 b1 b1 | b2 b2 b0 b1
+// -> a0b0 a1b0 a0b1 a1b1 | a0b2 a1b2 a2b0 a2b1, the same eight products as the staged kernel's.
+__device__ __forceinline__ uint2 scale_frag_a(float s, bool h) {
+    uint32_t p0, p1, p2;
+    split_bf16x3(s, p0, p1, p2);
+    const uint32_t p01 = bf16_pair(p0, p1);
+    return make_uint2(p01, h ? bf16_pair(p2, p2) : p01);
+}
+__device__ __forceinline__ uint2 scale_frag_b(float s, bool h) {
+    uint32_t p0, p1, p2;
+    split_bf16x3(s, p0, p1, p2);
+    const uint32_t x = h ? p2 : p0, y = h ? p0 : p1;
+    return make_uint2(bf16_pair(x, x), bf16_pair(y, p1));
+}
+
+template <int FMT, int OUT, class C>
+__global__ __launch_bounds__(C::kThreads, C::EU) void gemm_direct_kernel(GemmArgs args) {
+    constexpr int WTM = C::WTM, WTN = C::WTN, NW = C::NW, U = C::U;
+    __shared__ float part[NW][C::kSlice][64];
+    __shared__ int32_t s_grp[2];
+    __shared__ int64_t s_pad;
+    const GemmJob& j = args.j;
+    Tile tl;
+    if (!resolve_tile<C::BM, C::BN>(j, s_grp, &s_pad, grid_pos(), tl)) return;
+    tl.a = uniform_ptr(tl.a);
+    tl.b = uniform_ptr(tl.b);
+    tl.as = uniform_ptr(tl.as);
+    tl.bs = uniform_ptr(tl.bs);
+    tl.a_row0 = __builtin_amdgcn_readfirstlane(tl.a_row0);
+    tl.b_row0 = __builtin_amdgcn_readfirstlane(tl.b_row0);
+    tl.mrows = __builtin_amdgcn_readfirstlane(tl.mrows);
+    tl.nrows = __builtin_amdgcn_readfirstlane(tl.nrows);
+    const int nkb = __builtin_amdgcn_readfirstlane((int)tl.nkb);
+
+    const int tid = threadIdx.x, lane = tid & 63, h = lane >> 5, l32 = lane & 31;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int ng = (nkb + U - 1) / U;  // groups of U blocks, dealt round robin to the waves
+
+    // resources that end at the tile's last valid byte; rows past it read zeros
+    const int64_t a_last = (tl.a_row0 + tl.mrows - 1) / kPanelRows, b_last = (tl.b_row0 + tl.nrows - 1) / kPanelRows;
+    const int a_cbytes = (int)(a_last * j.a_pld + (int64_t)nkb * kPanelBlockBytes);
+    const int a_sbytes = (int)((a_last * j.as_pld + (int64_t)nkb * kPanelBlockScales) * 4);
+    const int b_cbytes = (int)(b_last * j.b_pld + (int64_t)nkb * kPanelBlockBytes);
+    const int b_sbytes = (int)((b_last * j.bs_pld + (int64_t)nkb * kPanelBlockScales) * 4);
+    int voca[WTM], vosa[WTM], vocb[WTN], vosb[WTN];
+#pragma unroll
+    for (int a = 0; a < WTM; ++a) {
+        voca[a] = (int)code_off(tl.a_row0, a * 32 + l32, 0, j.a_pld) + 4 * h;  // the lane's K half: four bytes
+        vosa[a] = (int)scale_off(tl.a_row0, a * 32 + l32, 0, j.as_pld) * 4;
+    }
+#pragma unroll
+    for (int b = 0; b < WTN; ++b) {
+        vocb[b] = (int)code_off(tl.b_row0, b * 32 + l32, 0, j.b_pld) + 4 * h;
+        vosb[b] = (int)scale_off(tl.b_row0, b * 32 + l32, 0, j.bs_pld) * 4;
+    }
+
+    struct Group {  // codes and scales of the lane's rows, per block
+        uint32_t ac[U][WTM], as[U][WTM], bc[U][WTN], bs[U][WTN];
+    };
+    // a block past the reduction reads zeros (empty resources)
+    auto load = [&](Group& t, int g) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int kb = g * U + u;
+            const bool in = kb < nkb;
+            const int soc = __builtin_amdgcn_readfirstlane(kb * (int)kPanelBlockBytes);
+            const int sos = __builtin_amdgcn_readfirstlane(kb * (int)kPanelBlockScales * 4);
+#pragma unroll
+            for (int a = 0; a < WTM; ++a) {
+                t.ac[u][a] = __builtin_amdgcn_raw_buffer_load_b32(make_rsrc(tl.a, in ? a_cbytes : 0), voca[a], soc, 0);
+                t.as[u][a] = __builtin_amdgcn_raw_buffer_load_b32(make_rsrc(tl.as, in ? a_sbytes : 0), vosa[a], sos, 0);
+            }
+#pragma unroll
+            for (int b = 0; b < WTN; ++b) {
+                t.bc[u][b] = __builtin_amdgcn_raw_buffer_load_b32(make_rsrc(tl.b, in ? b_cbytes : 0), vocb[b], soc, 0);
+                t.bs[u][b] = __builtin_amdgcn_raw_buffer_load_b32(make_rsrc(tl.bs, in ? b_sbytes : 0), vosb[b], sos, 0);
+            }
+        }
+    };
+    auto conv = [](uint32_t d) -> uint2 {
+        if constexpr (FMT == kFmtUniform) return uniform_to_e4m3(d);
+        else return e2m1_to_e4m3(d);
+    };
+    float acc[WTM][WTN][16];
+#pragma unroll
+    for (int a = 0; a < WTM; ++a)
+#pragma unroll
+        for (int b = 0; b < WTN; ++b)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[a][b][i] = 0.0f;
+    auto compute = [&](const Group& t) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            uint2 ac[WTM], aw[WTM];
+#pragma unroll
+            for (int a = 0; a < WTM; ++a) {
+                ac[a] = conv(t.ac[u][a]);
+                aw[a] = scale_frag_a(__uint_as_float(t.as[u][a]), h);
+            }
+#pragma unroll
+            for (int b = 0; b < WTN; ++b) {
+                const uint2 bc = conv(t.bc[u][b]), bw = scale_frag_b(__uint_as_float(t.bs[u][b]), h);
+#pragma unroll
+                for (int a = 0; a < WTM; ++a) {
+                    const v16f d = block_dot(ac[a], bc);
+                    const v16f w = scale_outer(aw[a], bw);
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) acc[a][b][i] = __builtin_fmaf(d[i], w[i], acc[a][b][i]);
+                }
+            }
+        }
+    };
+    if (wave < ng) {
+        Group t0, t1;
+        load(t0, wave);
+        for (int g = wave; g < ng; g += 2 * NW) {
+            load(t1, g + NW);
+            compute(t0);
+            if (g + NW >= ng) break;
+            load(t0, g + 2 * NW);
+            compute(t1);
+        }
+    }
+
+    const float mul = FMT == kFmtUniform ? 262144.0f : 1.0f;  // uniform: the fp8 subnormal encoding's 2^-18
+#pragma unroll
+    for (int p = 0; p < C::kPasses; ++p) {
+        if (p > 0) __syncthreads();  // the previous slice has been read
+#pragma unroll
+        for (int i = 0; i < C::kSlice; ++i) {
+            const int e = p * C::kSlice + i;
+            part[wave][i][lane] = acc[e / 16 / WTN][e / 16 % WTN][e % 16];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < C::kSlice / NW; ++q) {
+            const int i = q * NW + wave, e = p * C::kSlice + i, t = e / 16, r = e % 16;
+            float sum = 0.0f;
+#pragma unroll
+            for (int w = 0; w < NW; ++w) sum += part[w][i][lane];
+            const int row = (t / WTN) * 32 + 8 * (r >> 2) + 4 * h + (r & 3), col = (t % WTN) * 32 + l32;
+            if (row < tl.mrows && col < tl.nrows) {
+                const float v = sum * mul;
+                const int64_t off = tl.c_off + (int64_t)row * j.ldc + col;
+                if constexpr (OUT == kOutF32) static_cast<float*>(j.c)[off] = v;
+                else static_cast<uint16_t*>(j.c)[off] = __builtin_bit_cast(uint16_t, (__bf16)v);  // RNE
             }
         }
     }
 }
 
-template <int FMT, int OUT>
-static hipError_t launch_t(const GemmJob& j, hipStream_t s) {
-    dim3 grid((unsigned)((j.N + BN - 1) / BN), 1, 1);
-    if (j.mode == kGemmRaggedM) {
-        grid.y = (unsigned)((j.M + BM - 1) / BM + j.G);
-    } else {
-        grid.y = (unsigned)((j.M + BM - 1) / BM);
-        if (j.mode == kGemmRaggedK) grid.z = (unsigned)j.G;
-    }
+using Direct32 = DirectCfg<1, 1, 8, 4, 4>;     // 32 x 32, 8 waves
+using Direct64 = DirectCfg<2, 2, 4, 2, 3>;     // 64 x 64, 4 waves
+
+template <int FMT, int OUT, class C>
+static hipError_t launch_direct(const GemmJob& j, hipStream_t s) {
+    const dim3 grid = gemm_grid(j, C::BM, C::BN);
     if (grid.x == 0 || grid.y == 0 || grid.z == 0) return hipSuccess;
     GemmArgs args{j};
-    gemm_f32_kernel<FMT, OUT><<<grid, 64 * kWaves2, 0, s>>>(args);
+    gemm_direct_kernel<FMT, OUT, C><<<grid, C::kThreads, 0, s>>>(args);
     return hipGetLastError();
+}
+
+// Which kernel takes a problem: the one with the smallest estimated time. A CU holds up to `resident` workgroups at
+// once, so a grid runs in rounds of 256 * resident workgroups:
+//     fixed + (rounds - 1) * again + blocks * ((rounds - 1) * round + slope[workgroups per CU in the last round - 1])
+// with slope[n - 1] the time per K-block of n workgroups sharing a CU and `round` that of a full round followed by
+// others, whose start hides its end. Microseconds, measured on gfx950 (256 CUs) on
+// grids of 1/4 to 8 workgroups per CU at K = 512, 2048 and 4096. The large tile stages least per output (an asymptotic
+// 111 cycles per 32 x 32 tile and block, against 127 for 128 x 64, 130 for the 64 x 64 and 186 for the 32 x 32 direct
+// tiles) but needs 512 tiles to fill the chip; smaller tiles and a split reduction give up some of that for a full chip
+// and a shorter chain per workgroup. Measured, us, 128 x 128 only -> picked: 256 x 512 x 256 8.7 -> 3.9, 64 x 4096 x
+// 4096 74 -> 10, 1024^3 22 -> 11, 1040 x 2064 x 1552 33 -> 24, 2048 x 2048 x 4096 76 -> 63, 2048 x 3072 x 2048 59 ->
+// 52; grids of many rounds keep the large tile.
+enum GemmKernel { kTile128, kTile128K2, kTile128x64, kDirect32, kDirect64, kGemmKernels };
+struct GemmCost {
+    int bm, bn, resident;
+    double fixed, again, round, slope[3];
+};
+constexpr GemmCost kGemmCost[kGemmKernels] = {
+    {Tile128::BM, Tile128::BN, 2, 5.0, 5.0, 0.405, {0.267, 0.442, 0.0}},
+    {Tile128K2::BM, Tile128K2::BN, 1, 7.0, 5.0, 0.217, {0.217, 0.0, 0.0}},
+    {Tile128x64::BM, Tile128x64::BN, 3, 5.0, 4.5, 0.345, {0.195, 0.245, 0.370}},
+    {Direct32::BM, Direct32::BN, 3, 3.6, 1.8, 0.060, {0.024, 0.046, 0.063}},
+    {Direct64::BM, Direct64::BN, 3, 6.0, 4.5, 0.188, {0.108, 0.129, 0.188}},
+};
+
+static GemmKernel pick_kernel(const GemmJob& j) {
+    constexpr double kCUs = 256.0;
+    // ragged-K: an average group; ragged-M: half a tile lost per group
+    const double blocks = j.mode == kGemmRaggedK ? (double)j.red_total / 16.0 / j.G : (double)j.nkb;
+    GemmKernel best = kTile128;
+    double best_us = 0.0;
+    for (int k = 0; k < kGemmKernels; ++k) {
+        const GemmCost& c = kGemmCost[k];
+        double rows = (double)((j.M + c.bm - 1) / c.bm);
+        if (j.mode == kGemmRaggedM) rows = (double)j.M / c.bm + 0.5 * j.G;
+        const double groups = rows * (double)((j.N + c.bn - 1) / c.bn) * (j.mode == kGemmRaggedK ? j.G : 1);
+        // the last round counts as partial even when it is full
+        const double per_cu = groups / kCUs, rounds = ceil(per_cu / c.resident), full = rounds > 1.0 ? rounds - 1.0 : 0.0;
+        const double rest = per_cu - full * c.resident;
+        const double last = c.slope[rest <= 1.0 ? 0 : rest <= 2.0 ? 1 : 2];
+        const double us = c.fixed + full * c.again + blocks * (full * c.round + last);
+        if (k == 0 || us < best_us) {
+            best = (GemmKernel)k;
+            best_us = us;
+        }
+    }
+    return best;
+}
+
+template <int FMT, int OUT>
+static hipError_t launch_picked(const GemmJob& j, hipStream_t s) {
+    switch (pick_kernel(j)) {
+        case kTile128K2: return launch_t<FMT, OUT, Tile128K2>(j, s);
+        case kTile128x64: return launch_t<FMT, OUT, Tile128x64>(j, s);
+        case kDirect32: return launch_direct<FMT, OUT, Direct32>(j, s);
+        case kDirect64: return launch_direct<FMT, OUT, Direct64>(j, s);
+        default: return launch_t<FMT, OUT, Tile128>(j, s);
+    }
 }
 
 hipError_t launch_gemm(const GemmJob& j, hipStream_t s) {
     if (j.format == kFmtE2M1) {
-        return j.out_dtype == kOutBF16 ? launch_t<kFmtE2M1, kOutBF16>(j, s) : launch_t<kFmtE2M1, kOutF32>(j, s);
+        return j.out_dtype == kOutBF16 ? launch_picked<kFmtE2M1, kOutBF16>(j, s) : launch_picked<kFmtE2M1, kOutF32>(j, s);
     }
-    return j.out_dtype == kOutBF16 ? launch_t<kFmtUniform, kOutBF16>(j, s) : launch_t<kFmtUniform, kOutF32>(j, s);
+    return j.out_dtype == kOutBF16 ? launch_picked<kFmtUniform, kOutBF16>(j, s) : launch_picked<kFmtUniform, kOutF32>(j, s);
 }
 
 }  // namespace ufp4
