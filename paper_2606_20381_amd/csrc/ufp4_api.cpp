@@ -727,10 +727,9 @@ int ufp4_mx_gemm_fwd_y_grouped(const ufp4_qtensor* x, const ufp4_qtensor* w, con
     j.nkb = x->red / 32;
     j.offsets = group_offsets_dev;
     j.G = num_groups;
-    j.m_tiles = ceil_div(x->rows, 256) + num_groups;
     j.b_group_rows = N;
     j.b_group_kb = 0;
-    if (j.m_tiles * ceil_div(N, 256) >= (int64_t(1) << 31)) return UFP4_ERR_UNSUPPORTED;
+    if ((ceil_div(x->rows, 256) + num_groups) * ceil_div(N, 256) >= (int64_t(1) << 31)) return UFP4_ERR_UNSUPPORTED;
     return status_of(launch_gemm_mx(j, static_cast<hipStream_t>(stream)));
 }
 
@@ -752,10 +751,9 @@ int ufp4_mx_gemm_bwd_dx_grouped(const ufp4_qtensor* dy, const ufp4_qtensor* wt, 
     j.nkb = dy->red / 32;
     j.offsets = group_offsets_dev;
     j.G = num_groups;
-    j.m_tiles = ceil_div(dy->rows, 256) + num_groups;
     j.b_group_rows = 0;
     j.b_group_kb = dy->red / 32;
-    if (j.m_tiles * ceil_div(j.N, 256) >= (int64_t(1) << 31)) return UFP4_ERR_UNSUPPORTED;
+    if ((ceil_div(dy->rows, 256) + num_groups) * ceil_div(j.N, 256) >= (int64_t(1) << 31)) return UFP4_ERR_UNSUPPORTED;
     return status_of(launch_gemm_mx(j, static_cast<hipStream_t>(stream)));
 }
 

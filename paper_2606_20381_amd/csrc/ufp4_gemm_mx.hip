@@ -9,7 +9,8 @@
 // reach them.
 //
 // Tiling: a 256 x 256 output tile per 512-thread workgroup (8 waves of 128 x 64, 4 x 2 MFMA tiles of 32 x 32,
-// two waves per SIMD, one workgroup per CU). K advances 128 (four 32-blocks) per stage. A stage of one panel
+// two waves per SIMD, one workgroup per CU); problems with too few such tiles take 128 x 128 or 64 x 64 ones (four
+// waves; see pick_mx). K advances 128 (four 32-blocks) per stage. A stage of one panel
 // is a contiguous 12 KiB run (the panel layout puts the 128 rows of a 32-block together, each row's 24 bytes
 // as three 8-byte units in three planes of 128 rows) plus 512 scale bytes; stages are copied unchanged from
 // global memory into a three-deep LDS ring by direct-to-LDS loads issued two stages ahead, and a lane's
@@ -17,30 +18,45 @@
 
 #include "ufp4_internal.h"
 
+#include <math.h>
+
 namespace ufp4 {
 
 typedef float v16f __attribute__((ext_vector_type(16)));
 typedef int v8i __attribute__((ext_vector_type(8)));
 
-constexpr int kMxTile = 256;                    // rows of A and of B per workgroup tile (two panels each)
-constexpr int kMxStageBlocks = 4;               // 32-blocks per stage
-constexpr int kMxStageBytes = kMxStageBlocks * 3072;  // one panel's codes per stage
-constexpr int kMxThreads = 512;                 // 8 waves, two per SIMD, each a 128 x 64 tile
-constexpr int kMxBufs = 3;                      // stages in LDS: the one computed and two in flight
-constexpr int kMxLoadsPerStage = 7;             // per wave: 3 of A, 3 of B, 1 of scales (16 bytes per lane)
+constexpr int kMxStageBlocks = 4;  // 32-blocks per stage
 
-struct MxStageSmem {
-    uint8_t a[2][kMxStageBytes];  // the tile's two panels of A
-    uint8_t b[2][kMxStageBytes];
-    uint8_t s[2][2][kMxStageBlocks * 128];  // scale bytes: [A, B][panel][block * 128 + row]
+// Tile configuration: WM x WN waves, each with WTM x WTN MFMA tiles of 32 x 32 outputs.
+template <int WTM_, int WTN_, int WM_, int WN_>
+struct MxCfg {
+    static constexpr int WTM = WTM_, WTN = WTN_, WM = WM_, WN = WN_;
+    static constexpr int BM = 32 * WTM * WM, BN = 32 * WTN * WN;
+    static constexpr int kWaves = WM * WN, kThreads = 64 * kWaves;
+    // 1 KiB direct-to-LDS loads of a stage: 96 code bytes per row of A and B, dealt to the waves, and each
+    // wave's share of the 4 scale bytes per row (16 bytes per lane)
+    static constexpr int kLoadsA = BM * 3 / 32, kLoadsB = BN * 3 / 32;
+    static constexpr int kWaveCodes = (kLoadsA + kLoadsB) / kWaves;
+    static constexpr int kScaleLanes = (BM + BN) / 4 / kWaves;
+    static constexpr int kWaveLoads = kWaveCodes + 1;
+    static_assert((kLoadsA + kLoadsB) % kWaves == 0 && kScaleLanes <= 64 && kWaves % 2 == 0,
+                  "every wave issues the same loads, and its scales belong to one operand");
 };
 
-// The 24 bytes of one row's 32-block: three 8-byte units 1024 bytes apart (planar layout, see the file
+template <class C>
+struct MxStageSmem {
+    uint8_t a[C::BM * 96];  // [panel][block][unit][row]: the panel layout, or its 64-row half
+    uint8_t b[C::BN * 96];
+    uint8_t s[C::BM * 4 + C::BN * 4];  // scale bytes of A, then of B: [panel][block][row]
+};
+
+// The 24 bytes of one row's 32-block: three 8-byte units PLANE bytes apart (planar layout, see the file
 // header), so 32 lanes reading consecutive rows touch 256 contiguous bytes per unit.
+template <int PLANE>
 __device__ __forceinline__ v8i load_fp6_operand(const uint8_t* p) {
     const uint2 x0 = *reinterpret_cast<const uint2*>(p);
-    const uint2 x1 = *reinterpret_cast<const uint2*>(p + 1024);
-    const uint2 x2 = *reinterpret_cast<const uint2*>(p + 2048);
+    const uint2 x1 = *reinterpret_cast<const uint2*>(p + PLANE);
+    const uint2 x2 = *reinterpret_cast<const uint2*>(p + 2 * PLANE);
     const v8i v = {(int)x0.x, (int)x0.y, (int)x1.x, (int)x1.y, (int)x2.x, (int)x2.y, 0, 0};
     return v;
 }
@@ -55,13 +71,12 @@ __device__ __forceinline__ void dma16(uint32_t voff, const void* sbase, const vo
                  : "memory", "m0");
 }
 
-// s_waitcnt immediates (gfx9 encoding): wait until at most n vector-memory operations are outstanding,
-// and additionally for all LDS operations.
-__device__ __forceinline__ void wait_vm_lgkm(int n) {
-    switch (n) {
-        case 0: __builtin_amdgcn_s_waitcnt(0x0070); break;
-        default: __builtin_amdgcn_s_waitcnt(0x0070 | kMxLoadsPerStage); break;
-    }
+// Wait until at most N vector-memory operations are outstanding, and for all LDS operations (s_waitcnt immediate, gfx9
+// encoding).
+template <int N>
+__device__ __forceinline__ void wait_vm_lgkm() {
+    static_assert(N < 16, "low bits of vmcnt only");
+    __builtin_amdgcn_s_waitcnt(0x0070 | N);
 }
 
 // Workgroup -> output tile. Workgroups are dealt to the 8 XCDs round robin (workgroup L to XCD L % 8) and each
@@ -89,12 +104,19 @@ __device__ __forceinline__ int64_t uniform_i64_mx(int64_t v) {
     return (int64_t)(((uint64_t)hi << 32) | lo);
 }
 
+// Ragged-M: a bound on the number of BM-row tiles over all groups (each group may end in a partial tile).
+template <int BM>
+__host__ __device__ inline int64_t mx_ragged_tiles(const MxGemmJob& j) {
+    return (j.a_rows + BM - 1) / BM + j.G;
+}
+
 // Ragged-M: the group and local tile of global m-tile t, with the group's padded row start (a multiple of 128)
-// and its token rows. Wave 0 prefix-sums the per-group tile counts ceil(m_g / 256) and padded lengths
+// and its token rows. Wave 0 prefix-sums the per-group tile counts ceil(m_g / BM) and padded lengths
 // pad128(m_g), 64 groups at a time; the result goes through LDS. Every thread calls this; false past the last tile.
 struct MxGroupTile {
     int64_t g, lt, prow0, trow0, rows;
 };
+template <int BM>
 __device__ bool resolve_mx_ragged_m(const MxGemmJob& j, int64_t t, int64_t* slot, MxGroupTile& r) {
     const int tid = threadIdx.x;
     if (tid == 0) slot[0] = -1;
@@ -106,7 +128,7 @@ __device__ bool resolve_mx_ragged_m(const MxGemmJob& j, int64_t t, int64_t* slot
             int64_t m = 0;
             if (g < j.G) m = j.offsets[g + 1] - j.offsets[g];
             if (m < 0) m = 0;
-            const int64_t cnt = (m + kMxTile - 1) / kMxTile, pad = (m + 127) / 128 * 128;
+            const int64_t cnt = (m + BM - 1) / BM, pad = (m + 127) / 128 * 128;
             int64_t ti = cnt, pi = pad;
 #pragma unroll
             for (int d = 1; d < 64; d <<= 1) {
@@ -131,9 +153,9 @@ __device__ bool resolve_mx_ragged_m(const MxGemmJob& j, int64_t t, int64_t* slot
     r.g = slot[0];
     if (r.g < 0) return false;
     r.lt = slot[1];
-    r.prow0 = slot[2] + r.lt * kMxTile;
-    r.trow0 = j.offsets[r.g] + r.lt * kMxTile;
-    r.rows = slot[3] - r.lt * kMxTile;
+    r.prow0 = slot[2] + r.lt * BM;
+    r.trow0 = j.offsets[r.g] + r.lt * BM;
+    r.rows = slot[3] - r.lt * BM;
     return true;
 }
 
@@ -157,30 +179,32 @@ __device__ void mx_padded_range(const int64_t* off, int g, int64_t* slot, int64_
     len = (c > 0 ? c + kMxBlock32 - 1 : 0) / kMxBlock32 * kMxBlock32;
 }
 
-template <int OUT>
-__global__ __launch_bounds__(kMxThreads) void gemm_mx_kernel(MxGemmJob j) {
+template <int OUT, class C>
+__global__ __launch_bounds__(C::kThreads) void gemm_mx_kernel(MxGemmJob j) {
     // three separate LDS objects (not an array): the compiler then knows that loads in flight into one buffer
     // do not alias reads of another and does not make the reads wait for them
-    __shared__ MxStageSmem sm0, sm1, sm2;
+    __shared__ MxStageSmem<C> sm0, sm1, sm2;
     __shared__ int64_t s_slot[4];
+    constexpr int BM = C::BM, BN = C::BN;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform: load addresses stay scalar
     const int h = lane >> 5, l32 = lane & 31;
-    const int wm = wave >> 2, wn = wave & 3;  // wave tile: rows wm * 128 .. + 127, cols wn * 64 .. + 63
+    const int wm = (int)((unsigned)wave / C::WN), wn = (int)((unsigned)wave % C::WN);
     int64_t tm, tn;
-    const int64_t gy = j.mode == kGemmRaggedM ? j.m_tiles : (j.M + kMxTile - 1) / kMxTile;
-    tile_of(blockIdx.x, gy, (j.N + kMxTile - 1) / kMxTile, tm, tn);
-    // What the tile covers: A panels from pa0, B panels from pb0, reduction blocks from a_kb0 / b_kb0 (nkb of
-    // them), output rows out_row0 .. out_row0 + mrows - 1 (token rows for ragged-M) of the problem at c_base.
-    int64_t pa0 = 2 * tm, pb0 = 2 * tn, a_kb0 = 0, b_kb0 = 0, nkb64 = j.nkb;
-    int64_t out_row0 = tm * kMxTile, mrows = j.M - tm * kMxTile, c_base = 0;
+    const int64_t gy = j.mode == kGemmRaggedM ? mx_ragged_tiles<BM>(j) : (j.M + BM - 1) / BM;
+    tile_of(blockIdx.x, gy, (j.N + BN - 1) / BN, tm, tn);
+    // What the tile covers: A rows from arow0 and B rows from brow0 of the operands, reduction blocks from a_kb0 /
+    // b_kb0 (nkb of them), output rows out_row0 .. out_row0 + mrows - 1 (token rows for ragged-M) of the problem at
+    // c_base.
+    int64_t arow0 = tm * BM, brow0 = tn * BN, a_kb0 = 0, b_kb0 = 0, nkb64 = j.nkb;
+    int64_t out_row0 = tm * BM, mrows = j.M - tm * BM, c_base = 0;
     if (j.mode == kGemmRaggedM) {
         MxGroupTile r;
-        if (!resolve_mx_ragged_m(j, tm, s_slot, r)) return;  // the whole workgroup agrees
-        pa0 = r.prow0 / 128;
+        if (!resolve_mx_ragged_m<BM>(j, tm, s_slot, r)) return;  // the whole workgroup agrees
+        arow0 = r.prow0;
         out_row0 = r.trow0;
         mrows = r.rows < j.M - r.trow0 ? r.rows : j.M - r.trow0;  // token rows past the output are not stored
-        pb0 = (r.g * j.b_group_rows) / 128 + 2 * tn;
+        brow0 = r.g * j.b_group_rows + tn * BN;
         b_kb0 = r.g * j.b_group_kb;
     } else if (j.mode == kGemmRaggedK) {
         int64_t start, len;
@@ -190,84 +214,101 @@ __global__ __launch_bounds__(kMxThreads) void gemm_mx_kernel(MxGemmJob j) {
         if (a_kb0 + nkb64 > j.nkb) nkb64 = j.nkb - a_kb0 > 0 ? j.nkb - a_kb0 : 0;  // clamped to the operands
         c_base = (int64_t)blockIdx.y * j.M * j.ldc;
     }
-    pa0 = uniform_i64_mx(pa0);
-    pb0 = uniform_i64_mx(pb0);
+    arow0 = uniform_i64_mx(arow0);
+    brow0 = uniform_i64_mx(brow0);
     a_kb0 = uniform_i64_mx(a_kb0);
     b_kb0 = uniform_i64_mx(b_kb0);
     nkb64 = uniform_i64_mx(nkb64);
-    // The tile's two panels of each operand. A panel past the operand's last one (a tile over the edge) is
-    // replaced by the last panel: those rows only feed outputs that are not stored.
+    // The tile's panels (two of a 256-row tile) and, for a 64-row tile, its half of the panel. A panel past the
+    // operand's last one (a tile over the edge) is replaced by the last panel: those rows only feed outputs that are
+    // not stored.
     const int64_t pa_last = (j.a_rows - 1) / 128, pb_last = (j.b_rows - 1) / 128;
+    int64_t pa0 = arow0 / 128, pb0 = brow0 / 128;
     if (pa0 > pa_last) pa0 = pa_last;  // only for offsets inconsistent with the operand: wrong values, no fault
     if (pb0 > pb_last) pb0 = pb_last;
     const int64_t pa1 = pa0 + 1 < pa_last ? pa0 + 1 : pa_last;
     const int64_t pb1 = pb0 + 1 < pb_last ? pb0 + 1 : pb_last;
-    const uint8_t* const ga0 = j.a + pa0 * j.a_pld + a_kb0 * 3072;
+    const int a_half = BM == 64 ? (int)((arow0 / 64) & 1) : 0, b_half = BN == 64 ? (int)((brow0 / 64) & 1) : 0;
+    const uint8_t* const ga0 = j.a + pa0 * j.a_pld + a_kb0 * 3072 + a_half * 512;
     const uint8_t* const ga1 = j.a + pa1 * j.a_pld + a_kb0 * 3072;
-    const uint8_t* const gb0 = j.b + pb0 * j.b_pld + b_kb0 * 3072;
+    const uint8_t* const gb0 = j.b + pb0 * j.b_pld + b_kb0 * 3072 + b_half * 512;
     const uint8_t* const gb1 = j.b + pb1 * j.b_pld + b_kb0 * 3072;
-    // this wave's scale run: chunks 16 w .. 16 w + 15 of [A panel 0, A panel 1, B panel 0, B panel 1] x 32
-    const int sop = wave >> 2, sp = (wave >> 1) & 1;
-    const uint8_t* const gs = sop == 0 ? j.as + (sp ? pa1 : pa0) * j.as_pld + a_kb0 * 128
-                                       : j.bs + (sp ? pb1 : pb0) * j.bs_pld + b_kb0 * 128;
+    // This wave's scale run: chunks (16 bytes) kScaleLanes w .. of [A, B] x [panel][block][row]. The first half of the
+    // waves take A's (square tiles).
+    static_assert(BM == BN, "the waves' scale shares divide between the operands");
+    const int sop = wave >= C::kWaves / 2;
+    const int sc0 = (wave - sop * (C::kWaves / 2)) * C::kScaleLanes;  // first chunk within the operand
+    constexpr int kBlkChunks = (BM < 128 ? BM : 128) / 16;                 // chunks of one block of a panel
+    const int spanel = sc0 / (kBlkChunks * kMxStageBlocks);
+    const uint8_t* const gs = sop == 0 ? j.as + (spanel ? pa1 : pa0) * j.as_pld + a_kb0 * 128 + a_half * 64
+                                       : j.bs + (spanel ? pb1 : pb0) * j.bs_pld + b_kb0 * 128 + b_half * 64;
     const int64_t N = j.N, ldc = j.ldc;
     void* const cptr = j.c;
     const int nkb = (int)nkb64;
     const int nst = (nkb + kMxStageBlocks - 1) / kMxStageBlocks;
     const int kb_last = nkb - 1;
 
-    // Stage s into a buffer with direct global-to-LDS loads: each wave instruction moves 64 x 16 bytes to
-    // 1024 contiguous LDS bytes. Per operand a stage is 2 panels x 768 chunks; wave w copies chunks
-    // i * 512 + w * 64 + lane (i < 3) of the pair, panel = chunk / 768, and scale chunks 16 w + lane (lanes
-    // 0-15). Every wave issues the same 7 loads for every stage: blocks past the end of the reduction
-    // (partial last stage) are read from the last block instead, and compute() gives them zero scales.
-    const uint32_t voff = (uint32_t)lane * 16;
-    auto issue = [&](int s, MxStageSmem& d) {
-        const int kb0 = s * kMxStageBlocks;
+    // A stage with direct global-to-LDS loads: each wave instruction moves 64 x 16 bytes to 1024 contiguous LDS bytes
+    // (the loads of A, then those of B, dealt round robin to the waves). Every wave issues the same number of
+    // loads for every stage: blocks past the end of the reduction (partial last stage) are read from the last block
+    // instead, and compute() gives them zero scales.
+    auto issue = [&](int i, MxStageSmem<C>& d) {
+        const int kb0 = i * kMxStageBlocks;
 #pragma unroll
-        for (int i = 0; i < 3; ++i) {
-            const int c0 = i * 512 + wave * 64;  // 64-chunk groups never straddle a panel or a block
-            const int p = c0 / 768, cp0 = c0 - p * 768, blk = cp0 / 192;
-            const int kb = kb0 + blk < kb_last ? kb0 + blk : kb_last;
-            const int64_t off = (int64_t)kb * 3072 + (cp0 - blk * 192) * 16;
-            dma16(voff, (p ? ga1 : ga0) + off, reinterpret_cast<uint4*>(d.a[p]) + cp0);
-            dma16(voff, (p ? gb1 : gb0) + off, reinterpret_cast<uint4*>(d.b[p]) + cp0);
+        for (int q = 0; q < C::kWaveCodes; ++q) {
+            const int Lall = q * C::kWaves + wave;
+            const bool isb = C::kLoadsA % C::kWaves == 0 ? q >= C::kLoadsA / C::kWaves : Lall >= C::kLoadsA;
+            const int L = isb ? Lall - C::kLoadsA : Lall;
+            const uint8_t* const g0 = isb ? gb0 : ga0;
+            const uint8_t* const g1 = isb ? gb1 : ga1;
+            uint8_t* const dst = (isb ? d.b : d.a) + L * 1024;
+            if constexpr (BM >= 128) {  // whole panels: a load lies in one block
+                const int p = L / 12, cp0 = (L - p * 12) * 64, blk = cp0 / 192;
+                const int kb = kb0 + blk < kb_last ? kb0 + blk : kb_last;
+                const int64_t off = (int64_t)kb * 3072 + (cp0 - blk * 192) * 16;
+                dma16((uint32_t)lane * 16, (p ? g1 : g0) + off, dst);
+            } else {  // half a panel: a load is two 512-byte runs (one unit of one block each)
+                const int run = 2 * L + h, blk = run / 3, unit = run - blk * 3;
+                const int kb = kb0 + blk < kb_last ? kb0 + blk : kb_last;
+                dma16((uint32_t)kb * 3072u + (uint32_t)(unit * 1024 + l32 * 16), g0, dst);
+            }
         }
-        if (lane < 16) {
-            const int cc = (wave & 1) * 16 + lane, blk = cc >> 3;  // chunk within the 32-chunk run
+        if (lane < C::kScaleLanes) {
+            const int cc = sc0 % (kBlkChunks * kMxStageBlocks) + lane, blk = cc / kBlkChunks;  // chunk within the panel
             const int kb = kb0 + blk < kb_last ? kb0 + blk : kb_last;
-            dma16((uint32_t)(kb * 128 + (cc & 7) * 16), gs, reinterpret_cast<uint4*>(&d.s[0][0][0]) + wave * 16);
+            dma16((uint32_t)(kb * 128 + (cc % kBlkChunks) * 16), gs, d.s + sop * BM * 4 + sc0 * 16);
         }
     };
 
-    v16f acc[4][2];
+    v16f acc[C::WTM][C::WTN];
 #pragma unroll
-    for (int a = 0; a < 4; ++a)
+    for (int a = 0; a < C::WTM; ++a)
 #pragma unroll
-        for (int b = 0; b < 2; ++b)
+        for (int b = 0; b < C::WTN; ++b)
 #pragma unroll
             for (int i = 0; i < 16; ++i) acc[a][b][i] = 0.0f;
 
-    auto compute = [&](const MxStageSmem& d, int valid) {
+    constexpr int kPlane = BM < 128 ? BM * 8 : 1024, kRowsP = BM < 128 ? BM : 128;  // LDS panel (or half panel)
+    auto compute = [&](const MxStageSmem<C>& d, int valid) {
 #pragma unroll
         for (int ks = 0; ks < kMxStageBlocks / 2; ++ks) {
             const int kk = 2 * ks + h;  // this lane's 32-block: lanes 0-31 hold K 0-31 of the step, 32-63 K 32-63
             const bool live = kk < valid;  // blocks past the end get scale 2^-127 on both sides: products 0
-            v8i av[4], bv[2];
-            int sa[4], sb[2];
+            v8i av[C::WTM], bv[C::WTN];
+            int sa[C::WTM], sb[C::WTN];
 #pragma unroll
-            for (int b = 0; b < 2; ++b) {
-                const int col = wn * 64 + b * 32 + l32, p = col >> 7, r = col & 127;
-                bv[b] = load_fp6_operand(d.b[p] + kk * 3072 + r * 8);
-                sb[b] = live ? d.s[1][p][kk * 128 + r] : 0;
+            for (int b = 0; b < C::WTN; ++b) {
+                const int col = (wn * C::WTN + b) * 32 + l32, p = col / kRowsP, r = col % kRowsP;
+                bv[b] = load_fp6_operand<kPlane>(d.b + (p * kMxStageBlocks + kk) * 3 * kPlane + r * 8);
+                sb[b] = live ? d.s[BM * 4 + (p * kMxStageBlocks + kk) * kRowsP + r] : 0;
             }
 #pragma unroll
-            for (int a = 0; a < 4; ++a) {
-                const int r = a * 32 + l32;  // row within panel wm
-                av[a] = load_fp6_operand(d.a[wm] + kk * 3072 + r * 8);
-                sa[a] = live ? d.s[0][wm][kk * 128 + r] : 0;
+            for (int a = 0; a < C::WTM; ++a) {
+                const int row = (wm * C::WTM + a) * 32 + l32, p = (wm * C::WTM + a) * 32 / kRowsP, r = row % kRowsP;
+                av[a] = load_fp6_operand<kPlane>(d.a + (p * kMxStageBlocks + kk) * 3 * kPlane + r * 8);
+                sa[a] = live ? d.s[(p * kMxStageBlocks + kk) * kRowsP + r] : 0;
 #pragma unroll
-                for (int b = 0; b < 2; ++b)
+                for (int b = 0; b < C::WTN; ++b)
                     // formats 2 = FP6 E2M3 for both operands; the scale bytes sit in byte 0 of sa / sb
                     acc[a][b] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(av[a], bv[b], acc[a][b], 2, 2, 0,
                                                                                 sa[a], 0, sb[b]);
@@ -275,28 +316,29 @@ __global__ __launch_bounds__(kMxThreads) void gemm_mx_kernel(MxGemmJob j) {
         }
     };
 
-    // Stage s is computed from buffer s % 3 while stages s + 1 and s + 2 are in flight. A wave's own loads
-    // of stage s are complete once at most the 7 of stage s + 1 are outstanding; the barrier then makes every
-    // wave's part visible, and it also orders the previous stage's reads of buffer (s + 2) % 3 before the
+    // Stage i is computed from buffer i % 3 while stages i + 1 and i + 2 are in flight. A wave's own loads
+    // of stage i are complete once at most those of stage i + 1 are outstanding; the barrier then makes every
+    // wave's part visible, and it also orders the previous stage's reads of buffer (i + 2) % 3 before the
     // loads into it are issued.
-    auto step = [&](int s, MxStageSmem& cur, MxStageSmem& next2) {
-        wait_vm_lgkm(s + 1 < nst ? kMxLoadsPerStage : 0);
+    auto step = [&](int i, MxStageSmem<C>& cur, MxStageSmem<C>& next2) {
+        if (i + 1 < nst) wait_vm_lgkm<C::kWaveLoads>();
+        else wait_vm_lgkm<0>();
         __builtin_amdgcn_s_barrier();
-        if (s + 2 < nst) issue(s + 2, next2);
-        const int left = nkb - s * kMxStageBlocks;
+        if (i + 2 < nst) issue(i + 2, next2);
+        const int left = nkb - i * kMxStageBlocks;
         compute(cur, left < kMxStageBlocks ? left : kMxStageBlocks);
     };
     if (nst > 0) issue(0, sm0);
     if (nst > 1) issue(1, sm1);
-    for (int s = 0; s < nst; s += 3) {
-        step(s, sm0, sm2);
-        if (s + 1 < nst) step(s + 1, sm1, sm0);
-        if (s + 2 < nst) step(s + 2, sm2, sm1);
+    for (int i = 0; i < nst; i += 3) {
+        step(i, sm0, sm2);
+        if (i + 1 < nst) step(i + 1, sm1, sm0);
+        if (i + 2 < nst) step(i + 2, sm2, sm1);
     }
 
     // Epilogue: lane (l32, h) holds rows 8q + 4h + t (q, t < 4) of column l32 of each 32 x 32 tile; a store
     // instruction writes two runs of 32 consecutive outputs. Tiles inside the output skip the bounds tests.
-    const bool inside = mrows >= kMxTile && (tn + 1) * kMxTile <= N;
+    const bool inside = mrows >= BM && (tn + 1) * BN <= N;
     auto store = [&](int64_t row, int64_t col, float v) {
         const int64_t off = c_base + row * ldc + col;
         if constexpr (OUT == kOutF32) {
@@ -306,11 +348,11 @@ __global__ __launch_bounds__(kMxThreads) void gemm_mx_kernel(MxGemmJob j) {
         }
     };
 #pragma unroll
-    for (int a = 0; a < 4; ++a) {
+    for (int a = 0; a < C::WTM; ++a) {
 #pragma unroll
-        for (int b = 0; b < 2; ++b) {
-            const int64_t col = tn * kMxTile + wn * 64 + b * 32 + l32;
-            const int64_t lr0 = wm * 128 + a * 32 + 4 * h;  // tile row of acc element 0
+        for (int b = 0; b < C::WTN; ++b) {
+            const int64_t col = tn * BN + (wn * C::WTN + b) * 32 + l32;
+            const int64_t lr0 = (wm * C::WTM + a) * 32 + 4 * h;  // tile row of acc element 0
             if (inside) {
 #pragma unroll
                 for (int i = 0; i < 16; ++i) store(out_row0 + lr0 + 8 * (i >> 2) + (i & 3), col, acc[a][b][i]);
@@ -325,14 +367,76 @@ __global__ __launch_bounds__(kMxThreads) void gemm_mx_kernel(MxGemmJob j) {
     }
 }
 
-hipError_t launch_gemm_mx(const MxGemmJob& j, hipStream_t s) {
-    const int64_t gy = j.mode == kGemmRaggedM ? j.m_tiles : (j.M + kMxTile - 1) / kMxTile;
-    const int64_t tiles = ((j.N + kMxTile - 1) / kMxTile) * gy;
+using MxTile256 = MxCfg<4, 2, 2, 4>;  // 256 x 256, 8 waves of 128 x 64, two per SIMD, one workgroup per CU
+using MxTile128 = MxCfg<2, 2, 2, 2>;  // 128 x 128, 4 waves, two workgroups per CU
+using MxTile64 = MxCfg<1, 1, 2, 2>;   // 64 x 64, 4 waves, four workgroups per CU
+
+template <int OUT, class C>
+static hipError_t launch_mx_cfg(const MxGemmJob& j, hipStream_t s) {
+    const int64_t gy = j.mode == kGemmRaggedM ? mx_ragged_tiles<C::BM>(j) : (j.M + C::BM - 1) / C::BM;
+    const int64_t tiles = ((j.N + C::BN - 1) / C::BN) * gy;
     if (tiles == 0) return hipSuccess;
     const dim3 grid((unsigned)tiles, j.mode == kGemmRaggedK ? (unsigned)j.G : 1u);
-    if (j.out_dtype == kOutBF16) gemm_mx_kernel<kOutBF16><<<grid, kMxThreads, 0, s>>>(j);
-    else gemm_mx_kernel<kOutF32><<<grid, kMxThreads, 0, s>>>(j);
+    gemm_mx_kernel<OUT, C><<<grid, C::kThreads, 0, s>>>(j);
     return hipGetLastError();
+}
+
+// Which tile takes a problem: the one with the smallest estimated time. A CU holds `resident` workgroups at once, so a
+// grid runs in rounds of 256 * resident workgroups:
+//     fixed + (rounds - 1) * again + stages * ((rounds - 1) * round + slope[workgroups per CU in the last round - 1])
+// with slope[n - 1] the time per stage (128 of the reduction) of n workgroups sharing a CU and `round` that of a full
+// round followed by others. Microseconds, measured on gfx950 (256 CUs) on grids of 1/4 to 16 workgroups per CU at K =
+// 512, 2048 and 4096. The 256 x 256 tile moves the fewest operand bytes per output, and wins once its tiles fill the
+// chip; a smaller grid runs faster on more, smaller tiles with their shorter stages. Measured, us, 256 x 256 only ->
+// picked: 256 x 512 x 256 8.2 -> 3.8, 1024 x 3072 x 1024 15.1 -> 8.4, 1024 x 1024 x 3072 30.5 -> 9.7, 2048 x 2048 x
+// 8192 70.6 -> 33.4, 4096 x 2048 x 2048 24.5 -> 17.8; 4096^3 (45.5; 52.9 on 128 x 128) and larger keep the large tile.
+enum MxKernel { kMxTile256, kMxTile128, kMxTile64, kMxKernels };
+struct MxCost {
+    int tile, resident;
+    double fixed, again, round, slope[4];
+};
+constexpr MxCost kMxCost[kMxKernels] = {
+    {MxTile256::BM, 1, 7.5, 7.3, 1.19, {1.20, 0.0, 0.0, 0.0}},
+    {MxTile128::BM, 2, 5.0, 5.0, 0.66, {0.467, 0.700, 0.0, 0.0}},
+    {MxTile64::BM, 4, 3.5, 2.3, 0.62, {0.262, 0.326, 0.523, 0.647}},
+};
+
+static MxKernel pick_mx(const MxGemmJob& j) {
+    constexpr double kCUs = 256.0;
+    // ragged-K: an average group; ragged-M: half a tile lost per group
+    const double blocks = j.mode == kGemmRaggedK ? (double)j.nkb / j.G : (double)j.nkb;
+    const double stages = ceil(blocks / kMxStageBlocks);
+    MxKernel best = kMxTile256;
+    double best_us = 0.0;
+    for (int k = 0; k < kMxKernels; ++k) {
+        const MxCost& c = kMxCost[k];
+        const double rows = j.mode == kGemmRaggedM ? (double)j.M / c.tile + 0.5 * j.G : (double)((j.M + c.tile - 1) / c.tile);
+        const double groups = rows * (double)((j.N + c.tile - 1) / c.tile) * (j.mode == kGemmRaggedK ? j.G : 1);
+        // the last round counts as partial even when it is full
+        const double per_cu = groups / kCUs, rounds = ceil(per_cu / c.resident), full = rounds > 1.0 ? rounds - 1.0 : 0.0;
+        const double rest = per_cu - full * c.resident;
+        const double last = c.slope[rest <= 1.0 ? 0 : rest <= 2.0 ? 1 : rest <= 3.0 ? 2 : 3];
+        const double us = c.fixed + full * c.again + stages * (full * c.round + last);
+        if (k == kMxTile64 && j.nkb >= (int64_t(1) << 20)) continue;  // its load offsets are 32-bit
+        if (k == 0 || us < best_us) {
+            best = (MxKernel)k;
+            best_us = us;
+        }
+    }
+    return best;
+}
+
+template <int OUT>
+static hipError_t launch_mx_picked(const MxGemmJob& j, hipStream_t s) {
+    switch (pick_mx(j)) {
+        case kMxTile128: return launch_mx_cfg<OUT, MxTile128>(j, s);
+        case kMxTile64: return launch_mx_cfg<OUT, MxTile64>(j, s);
+        default: return launch_mx_cfg<OUT, MxTile256>(j, s);
+    }
+}
+
+hipError_t launch_gemm_mx(const MxGemmJob& j, hipStream_t s) {
+    return j.out_dtype == kOutBF16 ? launch_mx_picked<kOutBF16>(j, s) : launch_mx_picked<kOutF32>(j, s);
 }
 
 }  // namespace ufp4

@@ -166,7 +166,6 @@ struct MxGemmJob {
     int mode;
     const int64_t* offsets;
     int32_t G;
-    int64_t m_tiles;       // ragged-M: bound on the number of 256-row tiles over all groups
     int64_t b_group_rows;
     int64_t b_group_kb;
 };
