@@ -465,8 +465,10 @@ __global__ __launch_bounds__(C::kThreads, 4) void gemm_f32_kernel(GemmArgs args)
         }
         // the blocks of a partial last stage
         if (live) {
-#pragma unroll 1
-            for (int kb = 0; kb < nkb - nfull * C::kStageBlocks - C::SKB * wk && kb < C::SKB; ++kb) block(nfull & 1, kb);
+            const int left = nkb - nfull * C::kStageBlocks - C::SKB * wk;
+#pragma unroll
+            for (int kb = 0; kb < C::SKB; ++kb)
+                if (kb < left) block(nfull & 1, kb);
         }
     }
 
@@ -756,7 +758,8 @@ static GemmKernel pick_kernel(const GemmJob& j) {
         const double per_cu = groups / kCUs, rounds = ceil(per_cu / c.resident), full = rounds > 1.0 ? rounds - 1.0 : 0.0;
         const double rest = per_cu - full * c.resident;
         const double last = c.slope[rest <= 1.0 ? 0 : rest <= 2.0 ? 1 : 2];
-        const double us = c.fixed + full * c.again + blocks * (full * c.round + last);
+        double us = c.fixed + full * c.again + blocks * (full * c.round + last);
+        if (k == kTile128) us *= 0.96;  // the estimates' spread: within it the large tile stays
         if (k == 0 || us < best_us) {
             best = (GemmKernel)k;
             best_us = us;
