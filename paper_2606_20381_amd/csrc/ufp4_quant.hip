@@ -51,20 +51,32 @@ constexpr float kMagic8 = 12582920.0f;
 // are exact in fp32 (lo + u/2^16 needs at most 20 significant bits), so the decision is exact. Returns the
 // chosen integer.
 __device__ __forceinline__ float uniform_sr_level(float v, uint32_t u16) {
-    const float vc = __builtin_fminf(__builtin_fmaxf(v, -7.0f), 7.0f);
+    const float vc = __builtin_amdgcn_fmed3f(v, -7.0f, 7.0f);
     const float lo = floorf(vc);
     const float t = __builtin_fmaf((float)u16, 1.0f / 65536.0f, lo);
     return lo + ((t < vc) ? 1.0f : 0.0f);  // a zero level comes out as +0
 }
 
-// The same decision with the offset nibble as the result: lo + kMagic8 holds nibble lo + 8 in bits 0-3 (bits
-// 4-21 clear), and the step up is added to that bit pattern as an integer (lo + 8 + 1 <= 15: no carry leaves
-// the nibble, since lo = 7 only when the clamped v is 7, which never rounds up).
-__device__ __forceinline__ uint32_t uniform_sr_offset(float v, uint32_t u16) {
-    const float vc = __builtin_fminf(__builtin_fmaxf(v, -7.0f), 7.0f);
-    const float lo = floorf(vc);
-    const float t = __builtin_fmaf((float)u16, 1.0f / 65536.0f, lo);
-    return __float_as_uint(lo + kMagic8) + ((t < vc) ? 1u : 0u);
+// The same decision on integers. The rounded-up level is ceil(v - u / 2^16): with f = floor(-2^16 v) (exact: the product
+// is a power-of-two scaling) it is -((u + f) >> 16), so bits 16-19 of u + f are the two's complement nibble of the
+// negated level. v above 7 (by rounding, at most 7 (1 + 2^-23)) is cut to 7; below -7 the ceiling already gives -7.
+// Four instructions per element (scale, cut, floor, add with a word select of the draw) instead of eight for the
+// comparison on floats: the SR quantizers are VALU bound, and went from 430 to 367 instructions per block.
+__device__ __forceinline__ uint32_t uniform_sr_neg16(float v, uint32_t u16) {
+    const float f = __builtin_fmaxf(v * -65536.0f, -458752.0f);
+    int32_t i;
+    asm("v_cvt_flr_i32_f32 %0, %1" : "=v"(i) : "v"(f));
+    return u16 + (uint32_t)i;
+}
+
+// Bits 16-19 of eight words -> one dword of nibbles, element i in bits 4i .. 4i+3 (byte 2 of every word, even and odd
+// elements gathered apart).
+__device__ __forceinline__ uint32_t pack_nibbles16(const uint32_t* t) {
+    const uint32_t e = __builtin_amdgcn_perm(__builtin_amdgcn_perm(t[6], t[4], 0x0C0C0602u),
+                                             __builtin_amdgcn_perm(t[2], t[0], 0x0C0C0602u), 0x05040100u);
+    const uint32_t o = __builtin_amdgcn_perm(__builtin_amdgcn_perm(t[7], t[5], 0x0C0C0602u),
+                                             __builtin_amdgcn_perm(t[3], t[1], 0x0C0C0602u), 0x05040100u);
+    return (e & 0x0F0F0F0Fu) | ((o << 4) & 0xF0F0F0F0u);
 }
 
 // Eight words whose bits 0-3 hold a nibble and bits 4-21 are clear (higher bits arbitrary) -> one dword,
@@ -280,13 +292,19 @@ __device__ __forceinline__ bool quant_core(float (&y)[16], TFn&& exact_t, const 
         for (int i = 0; i < 16; ++i) {
             if constexpr (ROUND == kRoundSR) {
                 const uint32_t u16 = (i & 1) ? (u[i >> 1] >> 16) : (u[i >> 1] & 0xFFFFu);
-                tt[i] = uniform_sr_offset(v[i], u16);
+                tt[i] = uniform_sr_neg16(v[i], u16);
             } else {
                 tt[i] = __float_as_uint(v[i] + kMagic8);  // the rounding itself
             }
         }
-        code_lo = offset_to_sign_magnitude(pack_nibbles(tt));
-        code_hi = offset_to_sign_magnitude(pack_nibbles(tt + 8));
+        if constexpr (ROUND == kRoundSR) {
+            // nibbles of -k -> offset nibbles 8 + k = (-k ^ 7) + 1 (no carry: -k is never -8)
+            code_lo = offset_to_sign_magnitude((pack_nibbles16(tt) ^ 0x77777777u) + 0x11111111u);
+            code_hi = offset_to_sign_magnitude((pack_nibbles16(tt + 8) ^ 0x77777777u) + 0x11111111u);
+        } else {
+            code_lo = offset_to_sign_magnitude(pack_nibbles(tt));
+            code_hi = offset_to_sign_magnitude(pack_nibbles(tt + 8));
+        }
     } else {
         uint32_t lo = 0, hi = 0;
 #pragma unroll
@@ -546,7 +564,7 @@ constexpr int kXGD = 32;       // otherwise
 static_assert(kXC == 8 || kXC == 4, "columns per thread");
 
 template <int FMT, int ROUND, bool RHT, bool GROUPED, bool WIDE = false>
-__global__ __launch_bounds__(256) void quant_cols_kernel(const uint16_t* __restrict__ x, int64_t rows,
+__global__ __launch_bounds__(256, FMT == kFmtUniform && !WIDE ? 3 : 1) void quant_cols_kernel(const uint16_t* __restrict__ x, int64_t rows,
                                                              int64_t cols, int64_t prows, int64_t ld,
                                                              int64_t red_total, TGroups grp, QuantArgs qa,
                                                              uint8_t* __restrict__ codes, int64_t code_pld,
@@ -925,7 +943,7 @@ __device__ __forceinline__ void quant_block32_mx(const uint32_t (&w)[16], const 
                 const uint32_t u16 = (i & 1) ? (u[i >> 1] >> 16) : (u[i >> 1] & 0xFFFFu);
                 lv = uniform_sr_level(vi, u16);
             } else {
-                lv = __builtin_rintf(__builtin_fminf(__builtin_fmaxf(vi, -7.0f), 7.0f)) + 0.0f;
+                lv = __builtin_rintf(__builtin_amdgcn_fmed3f(vi, -7.0f, 7.0f)) + 0.0f;
             }
             if (i & 1) od[8 * h + (i >> 1)] = lv;
             else ev[8 * h + (i >> 1)] = lv;
@@ -1140,9 +1158,16 @@ static hipError_t launch_cols_t(const QuantJob& j, hipStream_t s) {
     const int64_t prows = padded_rows(j.qrows);
     const int64_t nblk = j.red / kBlock;
     constexpr int XG = WIDE ? kXG : kXGD, XB = 256 / XG;
-    const int64_t gy = (nblk + XB - 1) / XB;
+    const int64_t gx = (prows + XG * kXC - 1) / (XG * kXC);
+    int64_t gy = (nblk + XB - 1) / XB;
     if (prows == 0 || gy == 0) return hipSuccess;
-    const dim3 grid((unsigned)((prows + XG * kXC - 1) / (XG * kXC)), (unsigned)(gy < 65535 ? gy : 65535));
+    // Grouped: a workgroup first scans the group offsets (two barriers and the latency of their loads), so on a large
+    // tensor it takes several runs of XB blocks; the grid keeps eight workgroups per CU.
+    if (GROUPED) {
+        const int64_t runs = gx * gy / 2048;
+        gy = (gy + (runs < 1 ? 1 : runs > 8 ? 8 : runs) - 1) / (runs < 1 ? 1 : runs > 8 ? 8 : runs);
+    }
+    const dim3 grid((unsigned)gx, (unsigned)(gy < 65535 ? gy : 65535));
     TGroups grp{j.group_off, j.num_groups};
     quant_cols_kernel<FMT, ROUND, RHT, GROUPED, WIDE><<<grid, 256, 0, s>>>(
         static_cast<const uint16_t*>(j.x), j.xrows, j.qrows, prows, j.ld, j.red, grp, j.qa,
@@ -1311,18 +1336,16 @@ __global__ __launch_bounds__(256) void mx_tile_kernel(const uint16_t* __restrict
 }
 
 // Grouped operands: workgroup (tr, y) takes tile row tr of the operand's grouped axis and column tiles
-// kMxColChunk y .. kMxColChunk (y + 1) - 1, so that reading the group offsets is shared by a few tiles. GROWS
+// chunk y .. chunk (y + 1) - 1, so that reading the group offsets is shared by a few tiles. GROWS
 // (Q_r in grouped-rows form, for the ragged-M GEMMs): operand rows in panels, group g's rows X[off_g ..
 // off_{g+1}) from row P_g = sum_{h<g} pad128(m_h), the rest zero; a tile's 32 rows lie in one group's padded
 // range. Otherwise (Q_c with a grouped reduction, for bwd_dw): the reduction axis is each group's tokens padded
 // to 32, so the tile's 32 positions are rows src0 .. src0 + nvalid - 1 of X and zero padding.
-constexpr uint32_t kMxColChunk = 4;
-
 template <int ROUND, bool RHT, bool GROWS>
 __global__ __launch_bounds__(256) void mx_tile_grouped_kernel(const uint16_t* __restrict__ x, int64_t xrows,
                                                               int64_t cols, int64_t ld, uint32_t n_ctiles,
-                                                              int64_t qr_prows, TGroups grp, QuantArgs qa,
-                                                              MxTileOut o) {
+                                                              uint32_t chunk, int64_t qr_prows, TGroups grp,
+                                                              QuantArgs qa, MxTileOut o) {
     __shared__ int64_t s_off[kMaxGroupsLds + 1];
     __shared__ int64_t s_poff[kMaxGroupsLds + 1];
     __shared__ uint4 tile4[GROWS ? 1 : kMxTileWords / 4];
@@ -1342,8 +1365,8 @@ __global__ __launch_bounds__(256) void mx_tile_grouped_kernel(const uint16_t* __
         if (src0 < 0 || nvalid < 0) nvalid = 0;
         if (lr < nvalid) src = src0 + lr;
     }
-    const uint32_t tc_end = min(n_ctiles, (blockIdx.y + 1) * kMxColChunk);
-    for (uint32_t tc = blockIdx.y * kMxColChunk; tc < tc_end; ++tc) {
+    const uint32_t tc_end = min(n_ctiles, (blockIdx.y + 1) * chunk);
+    for (uint32_t tc = blockIdx.y * chunk; tc < tc_end; ++tc) {
         mx_tile<ROUND, RHT, RHT, GROWS, !GROWS>(x, cols, ld, src, r0 + lr, qr_prows, GROWS ? -1 : r0 / kMxBlock,
                                                 (int64_t)tc * 256, qa, qa, o, reinterpret_cast<uint32_t*>(tile4));
         if constexpr (!GROWS) __syncthreads();  // the tile's column reads before the next tile's writes
@@ -1403,13 +1426,16 @@ static hipError_t launch_mx_t(const MxQuantJob& j, hipStream_t s) {
         const int64_t n_ct = ((j.transpose ? padded_rows(cols) : cols) + 255) / 256;
         if (n_rt == 0 || n_ct == 0) return hipSuccess;
         const TGroups grp{j.group_off, j.num_groups};
-        const dim3 grid((unsigned)n_rt, (unsigned)((n_ct + kMxColChunk - 1) / kMxColChunk));
+        // column tiles per workgroup: up to four where that leaves eight workgroups per CU (measured: one tile is 13%
+        // faster than four on 9000 x 1280, sixteen 7% slower than four on 32768 x 5120)
+        const int64_t want = n_rt * n_ct / 2048, chunk = want < 1 ? 1 : want < 4 ? want : 4;
+        const dim3 grid((unsigned)n_rt, (unsigned)((n_ct + chunk - 1) / chunk));
         if (j.transpose)
             mx_tile_grouped_kernel<ROUND, RHT, false><<<grid, 256, 0, s>>>(
-                static_cast<const uint16_t*>(j.x), j.xrows, cols, j.ld, (uint32_t)n_ct, 0, grp, j.qa, o);
+                static_cast<const uint16_t*>(j.x), j.xrows, cols, j.ld, (uint32_t)n_ct, (uint32_t)chunk, 0, grp, j.qa, o);
         else
             mx_tile_grouped_kernel<ROUND, RHT, true><<<grid, 256, 0, s>>>(
-                static_cast<const uint16_t*>(j.x), j.xrows, cols, j.ld, (uint32_t)n_ct, j.qrows, grp, j.qa, o);
+                static_cast<const uint16_t*>(j.x), j.xrows, cols, j.ld, (uint32_t)n_ct, (uint32_t)chunk, j.qrows, grp, j.qa, o);
         return hipGetLastError();
     }
 }
