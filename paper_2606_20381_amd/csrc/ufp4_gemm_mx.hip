@@ -289,6 +289,8 @@ __global__ __launch_bounds__(C::kThreads) void gemm_mx_kernel(MxGemmJob j) {
             for (int i = 0; i < 16; ++i) acc[a][b][i] = 0.0f;
 
     constexpr int kPlane = BM < 128 ? BM * 8 : 1024, kRowsP = BM < 128 ? BM : 128;  // LDS panel (or half panel)
+    static_assert(kRowsP % (32 * C::WTM) == 0 && kRowsP % (32 * C::WTN) == 0, "a wave's rows lie in one LDS panel");
+    const unsigned arow = (unsigned)wm * C::WTM * 32, bcol = (unsigned)wn * C::WTN * 32;  // first tile row and column
     auto compute = [&](const MxStageSmem<C>& d, int valid) {
 #pragma unroll
         for (int ks = 0; ks < kMxStageBlocks / 2; ++ks) {
@@ -298,13 +300,13 @@ __global__ __launch_bounds__(C::kThreads) void gemm_mx_kernel(MxGemmJob j) {
             int sa[C::WTM], sb[C::WTN];
 #pragma unroll
             for (int b = 0; b < C::WTN; ++b) {
-                const int col = (wn * C::WTN + b) * 32 + l32, p = col / kRowsP, r = col % kRowsP;
+                const unsigned p = bcol / kRowsP, r = bcol % kRowsP + b * 32 + l32;
                 bv[b] = load_fp6_operand<kPlane>(d.b + (p * kMxStageBlocks + kk) * 3 * kPlane + r * 8);
                 sb[b] = live ? d.s[BM * 4 + (p * kMxStageBlocks + kk) * kRowsP + r] : 0;
             }
 #pragma unroll
             for (int a = 0; a < C::WTM; ++a) {
-                const int row = (wm * C::WTM + a) * 32 + l32, p = (wm * C::WTM + a) * 32 / kRowsP, r = row % kRowsP;
+                const unsigned p = arow / kRowsP, r = arow % kRowsP + a * 32 + l32;
                 av[a] = load_fp6_operand<kPlane>(d.a + (p * kMxStageBlocks + kk) * 3 * kPlane + r * 8);
                 sa[a] = live ? d.s[(p * kMxStageBlocks + kk) * kRowsP + r] : 0;
 #pragma unroll
