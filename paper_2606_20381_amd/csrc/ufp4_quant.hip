@@ -472,11 +472,10 @@ __global__ __launch_bounds__(kRT) void quant_rows_kernel(const T* __restrict__ x
 }
 
 // ------------------------------------------------------------------------------------------------
-// Transposed (and grouped-transposed): operand A = X^T, reduction along X's rows. A thread loads a
+// Transposed, large tensors (kTileElements): operand A = X^T, reduction along X's rows. A thread loads a
 // 16-row x kXC-column bf16 sub-tile (one load of 2 kXC bytes per row) and quantizes its kXC column blocks
 // from registers, so no LDS transposition and no barrier is needed. Its results are the kXC consecutive
-// operand rows of its block, 8 kXC contiguous bytes of codes (stored directly, or through LDS so that the
-// stores of a half-wave are contiguous; see the kernel). A workgroup of 256 threads covers 256 columns
+// operand rows of its block, 8 kXC contiguous bytes of codes. A workgroup of 256 threads covers 256 columns
 // x 8 blocks; the 32 threads of one block read 512 contiguous bytes of each row. (Measured on the 1 GiB
 // tensor: 64-column workgroups, 128 bytes per row, were 17% slower, wider ones no faster; 4 columns per
 // thread performs within a few percent of 8; an LDS-transposed 128 x 64 tile was 12-20% slower.)
@@ -495,6 +494,18 @@ __device__ __forceinline__ void load_row_chunk(const uint16_t* src, uint32_t (&d
 
 constexpr int kXC = 8;                     // columns (operand rows) per thread
 constexpr int kMaxGroupsLds = 1024;
+
+// The two outputs of the 16 x 256 tile kernels (those of Q_r unused without it).
+struct TileOut {
+    uint8_t* codes_r;
+    int64_t code_pld_r;
+    float* scales_r;
+    int64_t scale_pld_r;
+    uint8_t* codes_c;
+    int64_t code_pld_c;
+    float* scales_c;
+    int64_t scale_pld_c;
+};
 
 struct TGroups {
     const int64_t* off;  // token offsets [G+1] (device), nullptr for a dense tensor
@@ -558,54 +569,30 @@ __device__ __forceinline__ int find_group(const int64_t* s_poff, int G, int64_t 
 }
 
 // Column groups per workgroup. With 32 a wave reads 512 contiguous bytes of each row (two blocks of 256
-// columns); the block-n RHT kernel keeps 8 so that the m blocks of an n-block lie in one wave.
+// columns); the block-n RHT kernel (n = 32, see launch_cols_wide) keeps 8 so that the m blocks of an n-block lie in one
+// wave.
 constexpr int kXG = 64 / kXC;  // block-n RHT
 constexpr int kXGD = 32;       // otherwise
 static_assert(kXC == 8 || kXC == 4, "columns per thread");
 
-template <int FMT, int ROUND, bool RHT, bool GROUPED, bool WIDE = false>
-__global__ __launch_bounds__(256, FMT == kFmtUniform && !WIDE ? 3 : 1) void quant_cols_kernel(const uint16_t* __restrict__ x, int64_t rows,
-                                                             int64_t cols, int64_t prows, int64_t ld,
-                                                             int64_t red_total, TGroups grp, QuantArgs qa,
-                                                             uint8_t* __restrict__ codes, int64_t code_pld,
-                                                             float* __restrict__ scales, int64_t scale_pld) {
-    __shared__ int64_t s_off[GROUPED ? kMaxGroupsLds + 1 : 1];
-    __shared__ int64_t s_poff[GROUPED ? kMaxGroupsLds + 1 : 1];
+// The uniform grid is bounded to three waves per SIMD (SR: 178 -> 172 us on 16384^2); E2M1 would spill.
+template <int FMT, int ROUND, bool RHT, bool WIDE = false>
+__global__ __launch_bounds__(256, FMT == kFmtUniform && !WIDE ? 3 : 1) void quant_cols_kernel(
+    const uint16_t* __restrict__ x, int64_t rows, int64_t cols, int64_t prows, int64_t ld, int64_t red_total, QuantArgs qa,
+    uint8_t* __restrict__ codes, int64_t code_pld, float* __restrict__ scales, int64_t scale_pld) {
     const int t = threadIdx.x;
-    if constexpr (GROUPED) load_group_offsets<kBlock>(grp, s_off, s_poff);
     constexpr int XG = WIDE ? kXG : kXGD, XB = 256 / XG;  // column groups, blocks per workgroup
-    // Staged stores (dense RTNE): each half-wave (32 threads, one block of 256 operand rows) puts its 2 KB of
-    // codes and 1 KB of scales in its own LDS area in output order and reads them back so that every store
-    // instruction writes 512 contiguous bytes instead of 16-byte pieces of 64-byte runs. Measured on the 1 GiB
-    // tensor: 2% faster for uniform RTNE; SR, E2M1 and the grouped form would lose more to the extra registers
-    // (past 128 VGPRs) than they gain, so they store directly.
-    constexpr bool STAGE = !WIDE && !GROUPED && FMT == kFmtUniform && ROUND == kRoundRTNE && XG == 32 && kXC == 8;
-    __shared__ uint4 s_stage[STAGE ? 8 : 1][STAGE ? 192 : 1];
     const int cg = t % XG, rb = t / XG;
     const int64_t cbase = (int64_t)blockIdx.x * (XG * kXC) + cg * kXC;  // first operand row of the thread
-    // Without staging a thread past the last panel has nothing to do. With it, every thread stays: its (zero)
-    // data fills its slot of the stage and stores to panels past the end are skipped.
-    if (!STAGE && cbase >= prows) return;
+    if (cbase >= prows) return;
     const int ncol = cols - cbase < kXC ? (int)(cols - cbase) : kXC;  // valid columns of the thread (<= 0: none)
     const int64_t nblk = red_total / kBlock;
     constexpr int kW = kXC / 2;  // dwords per row
 
     for (int64_t gb = (int64_t)blockIdx.y * XB + rb; gb < nblk; gb += (int64_t)gridDim.y * XB) {
-        const int64_t P0 = gb * kBlock;
-        // the 16 positions of a block lie in one group (group lengths are padded to multiples of 16): rows
-        // src0 .. src0 + nvalid - 1 of X, the rest padding
-        int64_t src0, nvalid;
-        if constexpr (GROUPED) {
-            const int lo = find_group(s_poff, grp.G, P0);
-            const int64_t local0 = P0 - s_poff[lo];
-            src0 = s_off[lo] + local0;
-            nvalid = (s_off[lo + 1] - s_off[lo]) - local0;
-        } else {
-            src0 = P0;
-            nvalid = kBlock;
-        }
-        if (src0 + nvalid > rows) nvalid = rows - src0;  // offsets beyond X are treated as padding
-        if (src0 < 0 || nvalid < 0) nvalid = 0;
+        const int64_t src0 = gb * kBlock;
+        int64_t nvalid = kBlock;
+        if (src0 + nvalid > rows) nvalid = rows - src0;
 
         uint32_t v[kBlock][kW];
         if (ncol == kXC && nvalid == kBlock) {  // the common case: a full 16 x kXC sub-tile, no per-row tests
@@ -628,8 +615,8 @@ __global__ __launch_bounds__(256, FMT == kFmtUniform && !WIDE ? 3 : 1) void quan
                 }
             }
         }
-        // Columns past `cols` and rows past a group's tokens hold zeros: such a block quantizes to zero codes
-        // and a +0 scale, the padding value, so every block is quantized unconditionally.
+        // Columns past `cols` hold zeros: such a block quantizes to zero codes and a +0 scale, the padding value, so
+        // every block is quantized unconditionally.
         uint32_t clo[kXC], chi[kXC];
         float sc[kXC];
         uint32_t redo = 0;  // blocks outside the fast range (block-16 RHT or none), redone below
@@ -669,43 +656,13 @@ __global__ __launch_bounds__(256, FMT == kFmtUniform && !WIDE ? 3 : 1) void quan
                 }
             }
         }
-        if constexpr (STAGE) {
-            // half-wave area: codes of operand rows 0..255 of the block (8 bytes each, uint4 0..127), then their
-            // scales (uint4 128..191); thread cg owns rows 8 cg .. 8 cg + 7
-            uint4* st = s_stage[t >> 5];
-            const int L = t & 31;
+        const int64_t P = cbase >> 7, ri = cbase & 127;  // the kXC rows lie in one panel
+        uint4* dc = reinterpret_cast<uint4*>(codes + P * code_pld + gb * 1024 + ri * 8);
 #pragma unroll
-            for (int q = 0; q < 4; ++q) st[4 * L + q] = make_uint4(clo[2 * q], chi[2 * q], clo[2 * q + 1], chi[2 * q + 1]);
-            st[128 + 2 * L] = make_uint4(__float_as_uint(sc[0]), __float_as_uint(sc[1]), __float_as_uint(sc[2]),
-                                         __float_as_uint(sc[3]));
-            st[129 + 2 * L] = make_uint4(__float_as_uint(sc[4]), __float_as_uint(sc[5]), __float_as_uint(sc[6]),
-                                         __float_as_uint(sc[7]));
-            // the half-wave reads what its own lanes wrote: LDS operations of a wave complete in order, the wait
-            // and the compiler barrier keep the reads after the writes
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-            const int64_t P0 = (int64_t)blockIdx.x * 2;  // the block's two panels
+        for (int q = 0; q < kXC / 2; ++q) dc[q] = make_uint4(clo[2 * q], chi[2 * q], clo[2 * q + 1], chi[2 * q + 1]);
+        float4* ds = reinterpret_cast<float4*>(scales + P * scale_pld + gb * 128 + ri);
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int64_t P = P0 + (q >> 1);
-                if (P * kPanelRows < prows)
-                    *reinterpret_cast<uint4*>(codes + P * code_pld + gb * 1024 + (q & 1) * 512 + 16 * L) = st[32 * q + L];
-            }
-#pragma unroll
-            for (int q = 0; q < 2; ++q) {
-                const int64_t P = P0 + q;
-                if (P * kPanelRows < prows)
-                    *reinterpret_cast<uint4*>(scales + P * scale_pld + gb * 128 + 4 * L) = st[128 + 32 * q + L];
-            }
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // reads done before the next iteration's writes
-        } else {
-            const int64_t P = cbase >> 7, ri = cbase & 127;  // the kXC rows lie in one panel
-            uint4* dc = reinterpret_cast<uint4*>(codes + P * code_pld + gb * 1024 + ri * 8);
-#pragma unroll
-            for (int q = 0; q < kXC / 2; ++q) dc[q] = make_uint4(clo[2 * q], chi[2 * q], clo[2 * q + 1], chi[2 * q + 1]);
-            float4* ds = reinterpret_cast<float4*>(scales + P * scale_pld + gb * 128 + ri);
-#pragma unroll
-            for (int q = 0; q < kXC / 4; ++q) ds[q] = make_float4(sc[4 * q], sc[4 * q + 1], sc[4 * q + 2], sc[4 * q + 3]);
-        }
+        for (int q = 0; q < kXC / 4; ++q) ds[q] = make_float4(sc[4 * q], sc[4 * q + 1], sc[4 * q + 2], sc[4 * q + 3]);
     }
 }
 
@@ -860,6 +817,161 @@ __global__ __launch_bounds__(256) void quant_dual_kernel(const uint16_t* __restr
                 }
             }
         }
+    }
+}
+
+// ------------------------------------------------------------------------------------------------
+// The transposed operand, or both, by 16 x 256 tiles of X with one block per thread. Thread t loads 32 bytes of tile row
+// t % 16 (one block of that row), quantizes it for Q_r from its registers (DO_R), and leaves the words in LDS; after one
+// barrier it quantizes column t of the tile, one block of Q_c's row c0 + t. Sixteen lanes write 128 contiguous bytes of
+// Q_r's codes, a wave 512 of Q_c's.
+// ------------------------------------------------------------------------------------------------
+constexpr int kTileWords = 256 / 2 + 4;  // LDS words per tile row (16 bytes of padding)
+
+// One tile: columns c0 .. c0 + 255 of X, the thread's row of X (`src`, or -1: zeros), Q_r's row `qr_row` of it, and Q_c's
+// block `qc_blk` (-1: none).
+template <int FMT, int ROUND, bool RHT_R, bool RHT_C, bool DO_R>
+__device__ __forceinline__ void quant_tile(const uint16_t* __restrict__ x, int64_t cols, int64_t ld, int64_t src,
+                                           int64_t qr_row, int64_t qc_blk, int64_t c0, const QuantArgs& qr,
+                                           const QuantArgs& qc, const TileOut& o, uint4* tile4) {
+    const uint32_t* const tile = reinterpret_cast<const uint32_t*>(tile4);
+    const int t = threadIdx.x, lr = t & 15, lb = t >> 4;
+    const int64_t gc = c0 + lb * kBlock;
+    uint4 l0 = make_uint4(0, 0, 0, 0), l1 = l0;
+    if (src >= 0) {
+        const uint16_t* const sp = x + src * ld + gc;
+        if (gc + kBlock <= cols) {
+            l0 = reinterpret_cast<const uint4*>(sp)[0];
+            l1 = reinterpret_cast<const uint4*>(sp)[1];
+        } else if (!DO_R && gc < cols) {  // Q_c alone allows any column count: a partial block of the row
+            uint32_t w[8];
+            for (int i = 0; i < 8; ++i) {
+                const uint32_t lo = gc + 2 * i < cols ? sp[2 * i] : 0u, hi = gc + 2 * i + 1 < cols ? sp[2 * i + 1] : 0u;
+                w[i] = lo | (hi << 16);
+            }
+            l0 = make_uint4(w[0], w[1], w[2], w[3]);
+            l1 = make_uint4(w[4], w[5], w[6], w[7]);
+        }
+    }
+    tile4[lr * (kTileWords / 4) + 2 * lb] = l0;
+    tile4[lr * (kTileWords / 4) + 2 * lb + 1] = l1;
+    if constexpr (DO_R) {
+        if (gc < cols) {  // rows past the last one are zero padding (zero blocks: zero codes, a +0 scale)
+            const uint32_t w[8] = {l0.x, l0.y, l0.z, l0.w, l1.x, l1.y, l1.z, l1.w};
+            uint32_t lo, hi;
+            float sc;
+            quant_block16<FMT, ROUND, RHT_R>(w, qr, (uint32_t)(gc / kBlock), (uint32_t)qr_row, lo, hi, sc);
+            const int64_t P = qr_row >> 7, ri = qr_row & 127, b = gc / kBlock;
+            *reinterpret_cast<uint2*>(o.codes_r + P * o.code_pld_r + b * 1024 + ri * 8) = make_uint2(lo, hi);
+            o.scales_r[P * o.scale_pld_r + b * 128 + ri] = sc;
+        }
+    }
+    __syncthreads();
+    const int64_t cc = c0 + t;
+    if (qc_blk >= 0 && cc < padded_rows(cols)) {  // columns past the last one hold zeros: padding
+        const uint32_t sel = (t & 1) ? 0x07060302u : 0x05040100u;
+        uint32_t w[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+            w[j] = __builtin_amdgcn_perm(tile[(2 * j + 1) * kTileWords + (t >> 1)], tile[2 * j * kTileWords + (t >> 1)], sel);
+        uint32_t lo, hi;
+        float sc;
+        quant_block16<FMT, ROUND, RHT_C>(w, qc, (uint32_t)qc_blk, (uint32_t)cc, lo, hi, sc);
+        const int64_t P = cc >> 7, ri = cc & 127;
+        *reinterpret_cast<uint2*>(o.codes_c + P * o.code_pld_c + qc_blk * 1024 + ri * 8) = make_uint2(lo, hi);
+        o.scales_c[P * o.scale_pld_c + qc_blk * 128 + ri] = sc;
+    }
+}
+
+// Plain operands: `ngrp` groups of 16 rows (with Q_r's padding rows), a workgroup taking every gridDim.y-th one.
+template <int FMT, int ROUND, bool RHT_R, bool RHT_C, bool DO_R>
+__global__ __launch_bounds__(256) void quant_tile_kernel(const uint16_t* __restrict__ x, int64_t rows, int64_t cols,
+                                                         int64_t ld, int64_t ngrp, QuantArgs qr, QuantArgs qc,
+                                                         TileOut o) {
+    __shared__ uint4 tile4[kBlock * kTileWords / 4];
+    for (int64_t gb = blockIdx.y; gb < ngrp; gb += gridDim.y) {
+        if (gb != blockIdx.y) __syncthreads();  // the last tile's column reads before this one's writes
+        const int64_t gr = gb * kBlock + (threadIdx.x & 15);
+        quant_tile<FMT, ROUND, RHT_R, RHT_C, DO_R>(x, cols, ld, gr < rows ? gr : -1, gr, gb * kBlock < rows ? gb : -1,
+                                                   (int64_t)blockIdx.x * 256, qr, qc, o, tile4);
+    }
+}
+
+// Transposed operand after a block-n RHT, n = 16 M: tiles of 16 M x 256 / M, one 16-block per thread. The M threads of an
+// n-block (the sub-blocks of one column) are 64 / M lanes apart in one wave, where rht_wide exchanges their sums.
+template <int FMT, int ROUND, int M>
+__global__ __launch_bounds__(256) void quant_tile_wide_kernel(const uint16_t* __restrict__ x, int64_t cols, int64_t ld,
+                                                              int64_t nnb, QuantArgs qa, uint8_t* __restrict__ codes,
+                                                              int64_t code_pld, float* __restrict__ scales,
+                                                              int64_t scale_pld) {
+    constexpr int kCols = 256 / M, kW = kCols / 2 + 4, kStep = 64 / M;
+    __shared__ uint4 tile4[kBlock * M * kW / 4];
+    const uint32_t* const tile = reinterpret_cast<const uint32_t*>(tile4);
+    const int t = threadIdx.x;
+    const int lr = t % (kBlock * M), lb = t / (kBlock * M);  // this thread's load: 16 columns of a tile row
+    const int sub = t % 64 / kStep, c = t / 64 * kStep + t % kStep;  // its block: sub-block and column of the tile
+    const int64_t c0 = (int64_t)blockIdx.x * kCols, gc = c0 + lb * kBlock;
+    for (int64_t nb = blockIdx.y; nb < nnb; nb += gridDim.y) {
+        if (nb != blockIdx.y) __syncthreads();  // the last tile's column reads before this one's writes
+        uint4 l0 = make_uint4(0, 0, 0, 0), l1 = l0;
+        const uint16_t* const sp = x + (nb * kBlock * M + lr) * ld + gc;
+        if (gc + kBlock <= cols) {
+            l0 = reinterpret_cast<const uint4*>(sp)[0];
+            l1 = reinterpret_cast<const uint4*>(sp)[1];
+        } else if (gc < cols) {
+            uint32_t w[8];
+            for (int i = 0; i < 8; ++i) {
+                const uint32_t lo = gc + 2 * i < cols ? sp[2 * i] : 0u, hi = gc + 2 * i + 1 < cols ? sp[2 * i + 1] : 0u;
+                w[i] = lo | (hi << 16);
+            }
+            l0 = make_uint4(w[0], w[1], w[2], w[3]);
+            l1 = make_uint4(w[4], w[5], w[6], w[7]);
+        }
+        tile4[lr * (kW / 4) + 2 * lb] = l0;
+        tile4[lr * (kW / 4) + 2 * lb + 1] = l1;
+        __syncthreads();
+        const uint32_t sel = (c & 1) ? 0x07060302u : 0x05040100u;
+        const uint32_t* const col = tile + sub * kBlock * kW + (c >> 1);
+        uint32_t w[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) w[j] = __builtin_amdgcn_perm(col[(2 * j + 1) * kW], col[2 * j * kW], sel);
+        const int64_t gb = nb * M + sub, cc = c0 + c;
+        double tw[16];
+        rht_wide(w, qa, (uint32_t)gb, kStep, tw);  // every lane: columns past the last one hold zeros
+        if (cc < padded_rows(cols)) {
+            uint32_t lo, hi;
+            float sc;
+            quant_wide<FMT, ROUND>(tw, qa, (uint32_t)gb, (uint32_t)cc, lo, hi, sc);
+            const int64_t P = cc >> 7, ri = cc & 127;
+            *reinterpret_cast<uint2*>(codes + P * code_pld + gb * 1024 + ri * 8) = make_uint2(lo, hi);
+            scales[P * scale_pld + gb * 128 + ri] = sc;
+        }
+    }
+}
+
+// Grouped reduction: workgroup (x, y) takes block x of the padded token axis and column tiles chunk y .. chunk (y + 1) -
+// 1, so that reading the group offsets is shared by a few tiles. The block's 16 positions lie in one group (group lengths
+// are padded to multiples of 16): rows src0 .. src0 + nvalid - 1 of X and zero padding.
+template <int FMT, int ROUND, bool RHT>
+__global__ __launch_bounds__(256) void quant_tile_grouped_kernel(const uint16_t* __restrict__ x, int64_t xrows,
+                                                                 int64_t cols, int64_t ld, uint32_t n_ctiles,
+                                                                 uint32_t chunk, TGroups grp, QuantArgs qa, TileOut o) {
+    __shared__ int64_t s_off[kMaxGroupsLds + 1];
+    __shared__ int64_t s_poff[kMaxGroupsLds + 1];
+    __shared__ uint4 tile4[kBlock * kTileWords / 4];
+    load_group_offsets<kBlock>(grp, s_off, s_poff);
+    const int64_t P0 = (int64_t)blockIdx.x * kBlock;
+    const int g = find_group(s_poff, grp.G, P0);
+    const int64_t local0 = P0 - s_poff[g], src0 = s_off[g] + local0;
+    int64_t nvalid = s_off[g + 1] - s_off[g] - local0;
+    if (src0 + nvalid > xrows) nvalid = xrows - src0;  // offsets beyond X are treated as padding
+    if (src0 < 0 || nvalid < 0) nvalid = 0;
+    const int lr = threadIdx.x & 15;
+    const int64_t src = lr < nvalid ? src0 + lr : -1;
+    const uint32_t tc_end = min(n_ctiles, (blockIdx.y + 1) * chunk);
+    for (uint32_t tc = blockIdx.y * chunk; tc < tc_end; ++tc) {
+        quant_tile<FMT, ROUND, false, RHT, false>(x, cols, ld, src, 0, blockIdx.x, (int64_t)tc * 256, qa, qa, o, tile4);
+        __syncthreads();  // the tile's column reads before the next tile's writes
     }
 }
 
@@ -1153,26 +1265,91 @@ hipError_t launch_rht(const RhtJob& j, hipStream_t s) {
     return hipGetLastError();
 }
 
-template <int FMT, int ROUND, bool RHT, bool GROUPED, bool WIDE = false>
-static hipError_t launch_cols_t(const QuantJob& j, hipStream_t s) {
-    const int64_t prows = padded_rows(j.qrows);
-    const int64_t nblk = j.red / kBlock;
-    constexpr int XG = WIDE ? kXG : kXGD, XB = 256 / XG;
-    const int64_t gx = (prows + XG * kXC - 1) / (XG * kXC);
-    int64_t gy = (nblk + XB - 1) / XB;
-    if (prows == 0 || gy == 0) return hipSuccess;
-    // Grouped: a workgroup first scans the group offsets (two barriers and the latency of their loads), so on a large
-    // tensor it takes several runs of XB blocks; the grid keeps eight workgroups per CU.
-    if (GROUPED) {
-        const int64_t runs = gx * gy / 2048;
-        gy = (gy + (runs < 1 ? 1 : runs > 8 ? 8 : runs) - 1) / (runs < 1 ? 1 : runs > 8 ? 8 : runs);
-    }
-    const dim3 grid((unsigned)gx, (unsigned)(gy < 65535 ? gy : 65535));
-    TGroups grp{j.group_off, j.num_groups};
-    quant_cols_kernel<FMT, ROUND, RHT, GROUPED, WIDE><<<grid, 256, 0, s>>>(
-        static_cast<const uint16_t*>(j.x), j.xrows, j.qrows, prows, j.ld, j.red, grp, j.qa,
-        static_cast<uint8_t*>(j.codes), j.code_pld, j.scales, j.scale_pld);
+// Whether the 16 x 256 tile kernels take a tensor (else the register kernels, eight blocks per thread and operand). They
+// give a thread one block, which small tensors need to fill the chip, and run at full occupancy; the register kernels'
+// longer runs of stores win by 3-10% once a tensor is well past the 256 MiB memory-side cache. Measured, us, register ->
+// tile: two operands RTNE 256^2 9.1 -> 3.4, 2048^2 10.1 -> 6.1, 8192 x 4096 32.2 -> 28.3, 8192^2 52.9 -> 52.1, 32768 x
+// 16384 404 -> 432; transposed SR 2048^2 8.8 -> 5.2, 8192^2 43.6 -> 42.9, 32768 x 16384 329 -> 358. Transposed uniform
+// RTNE (537 Mi elements: 262 both) and E2M1 SR (32768 x 16384 785 -> 746, two operands 1541 -> 1432) stay on tiles.
+constexpr int64_t kTileElements = 100 << 20;
+template <int FMT, int ROUND, bool DUAL>
+constexpr bool kTileAlways = FMT == kFmtE2M1 ? ROUND == kRoundSR : !DUAL && ROUND == kRoundRTNE;
+
+// Column tiles per workgroup of the grouped kernels, whose group lookup they share: up to four where that leaves eight
+// workgroups per CU (measured on the power-of-two-scale kernel: one tile is 13% faster than four on 9000 x 1280, sixteen
+// 7% slower than four on 32768 x 5120), and as many as keep grid.y in range.
+static int64_t group_chunk(int64_t n_rt, int64_t n_ct) {
+    const int64_t want = n_rt * n_ct / 2048, chunk = want < 1 ? 1 : want < 4 ? want : 4, least = (n_ct + 65534) / 65535;
+    return chunk > least ? chunk : least;
+}
+
+static unsigned grid_y(int64_t n) { return (unsigned)(n < 65535 ? n : 65535); }
+
+template <int FMT, int ROUND, bool RHT>
+static hipError_t launch_cols_tile(const QuantJob& j, hipStream_t s) {
+    const int64_t nblk = j.red / kBlock, n_ct = (padded_rows(j.qrows) + 255) / 256;
+    const TileOut o{nullptr, 0, nullptr, 0, static_cast<uint8_t*>(j.codes), j.code_pld, j.scales, j.scale_pld};
+    quant_tile_kernel<FMT, ROUND, false, RHT, false><<<dim3((unsigned)n_ct, grid_y(nblk)), 256, 0, s>>>(
+        static_cast<const uint16_t*>(j.x), j.xrows, j.qrows, j.ld, nblk, j.qa, j.qa, o);
     return hipGetLastError();
+}
+
+template <int FMT, int ROUND, bool RHT>
+static hipError_t launch_cols_grouped(const QuantJob& j, hipStream_t s) {
+    const int64_t nblk = j.red / kBlock, n_ct = (padded_rows(j.qrows) + 255) / 256;
+    if (nblk == 0 || n_ct == 0) return hipSuccess;
+    const int64_t chunk = group_chunk(nblk, n_ct);
+    const TileOut o{nullptr, 0, nullptr, 0, static_cast<uint8_t*>(j.codes), j.code_pld, j.scales, j.scale_pld};
+    quant_tile_grouped_kernel<FMT, ROUND, RHT><<<dim3((unsigned)nblk, (unsigned)((n_ct + chunk - 1) / chunk)), 256, 0, s>>>(
+        static_cast<const uint16_t*>(j.x), j.xrows, j.qrows, j.ld, (uint32_t)n_ct, (uint32_t)chunk,
+        TGroups{j.group_off, j.num_groups}, j.qa, o);
+    return hipGetLastError();
+}
+
+template <int FMT, int ROUND, bool RHT, bool WIDE>
+static hipError_t launch_cols_regs(const QuantJob& j, hipStream_t s) {
+    constexpr int XG = WIDE ? kXG : kXGD, XB = 256 / XG;
+    const int64_t prows = padded_rows(j.qrows);
+    const dim3 grid((unsigned)((prows + XG * kXC - 1) / (XG * kXC)), grid_y((j.red / kBlock + XB - 1) / XB));
+    quant_cols_kernel<FMT, ROUND, RHT, WIDE><<<grid, 256, 0, s>>>(
+        static_cast<const uint16_t*>(j.x), j.xrows, j.qrows, prows, j.ld, j.red, j.qa, static_cast<uint8_t*>(j.codes),
+        j.code_pld, j.scales, j.scale_pld);
+    return hipGetLastError();
+}
+
+template <int FMT, int ROUND, bool RHT>
+static hipError_t launch_cols_t(const QuantJob& j, hipStream_t s) {
+    if (j.qrows == 0 || j.red / kBlock == 0) return hipSuccess;
+    if constexpr (kTileAlways<FMT, ROUND, false>) return launch_cols_tile<FMT, ROUND, RHT>(j, s);
+    else if (j.qrows * j.red <= kTileElements) return launch_cols_tile<FMT, ROUND, RHT>(j, s);
+    else return launch_cols_regs<FMT, ROUND, RHT, false>(j, s);
+}
+
+// RHT block of 16 M: the transposed operand (its reduction a multiple of 16 M). Large uniform RTNE tensors at n = 32 keep
+// the register kernel (32768 x 16384: 385 us, 428 on tiles); everywhere else the tiles are faster (8192^2: n = 32 54 -> 50
+// RTNE, 105 -> 60 SR; n = 64 74 -> 57 and 135 -> 70; n = 128 95 -> 83 and 167 -> 89; 4096 x 2048 12-22 -> 9-15).
+template <int FMT, int ROUND, int M>
+static hipError_t launch_cols_wide_m(const QuantJob& j, hipStream_t s) {
+    const int64_t prows = padded_rows(j.qrows), nnb = j.red / (kBlock * M);
+    if (prows == 0 || nnb == 0) return hipSuccess;
+    if constexpr (FMT == kFmtUniform && ROUND == kRoundRTNE && M == 2) {
+        if (j.qrows * j.red > kTileElements) return launch_cols_regs<FMT, ROUND, false, true>(j, s);
+    }
+    const dim3 grid((unsigned)((prows + 256 / M - 1) / (256 / M)), grid_y(nnb));
+    quant_tile_wide_kernel<FMT, ROUND, M><<<grid, 256, 0, s>>>(
+        static_cast<const uint16_t*>(j.x), j.qrows, j.ld, nnb, j.qa, static_cast<uint8_t*>(j.codes), j.code_pld, j.scales,
+        j.scale_pld);
+    return hipGetLastError();
+}
+
+template <int FMT, int ROUND>
+static hipError_t launch_cols_wide(const QuantJob& j, hipStream_t s) {
+    switch (j.qa.rht_m) {
+        case 2: return launch_cols_wide_m<FMT, ROUND, 2>(j, s);
+        case 4: return launch_cols_wide_m<FMT, ROUND, 4>(j, s);
+        case 8: return launch_cols_wide_m<FMT, ROUND, 8>(j, s);
+        default: return hipErrorInvalidValue;
+    }
 }
 
 template <int FMT, int ROUND, bool RHT>
@@ -1185,11 +1362,11 @@ static hipError_t dispatch_layout(const QuantJob& j, hipStream_t s) {
         if constexpr (!RHT) return hipErrorInvalidValue;
         else if (j.group_off) return hipErrorInvalidValue;
         else if (!j.transpose) return launch_rows_t<FMT, ROUND, false, uint16_t, true>(j, s);
-        else return launch_cols_t<FMT, ROUND, false, false, true>(j, s);
+        else return launch_cols_wide<FMT, ROUND>(j, s);
     }
     if (!j.transpose) return launch_rows_t<FMT, ROUND, RHT>(j, s);
-    if (j.group_off) return launch_cols_t<FMT, ROUND, RHT, true>(j, s);
-    return launch_cols_t<FMT, ROUND, RHT, false>(j, s);
+    if (j.group_off) return launch_cols_grouped<FMT, ROUND, RHT>(j, s);
+    return launch_cols_t<FMT, ROUND, RHT>(j, s);
 }
 
 template <int FMT>
@@ -1206,14 +1383,22 @@ hipError_t launch_quantize(const QuantJob& j, hipStream_t s) {
 
 template <int FMT, int ROUND, bool RHT_R, bool RHT_C>
 static hipError_t launch_dual_t(const DualJob& j, hipStream_t s) {
-    const int64_t gx = (padded_rows(j.cols) + 16 * kDC - 1) / (16 * kDC);
-    const int64_t gy = (padded_rows(j.rows) / kBlock + 4 * kDB - 1) / (4 * kDB);
-    if (gx == 0 || gy == 0) return hipSuccess;
-    const dim3 grid((unsigned)gx, (unsigned)(gy < 65535 ? gy : 65535));
-    quant_dual_kernel<FMT, ROUND, RHT_R, RHT_C><<<grid, 256, 0, s>>>(
-        static_cast<const uint16_t*>(j.x), j.rows, j.cols, j.ld, j.qr, j.qc, static_cast<uint8_t*>(j.codes_r),
-        j.code_pld_r, j.scales_r, j.scale_pld_r, static_cast<uint8_t*>(j.codes_c), j.code_pld_c, j.scales_c,
-        j.scale_pld_c);
+    const int64_t pcols = padded_rows(j.cols), ngrp = padded_rows(j.rows) / kBlock;
+    if (pcols == 0 || ngrp == 0) return hipSuccess;
+    const uint16_t* const x = static_cast<const uint16_t*>(j.x);
+    if (kTileAlways<FMT, ROUND, true> || j.rows * j.cols <= kTileElements) {
+        const TileOut o{static_cast<uint8_t*>(j.codes_r), j.code_pld_r, j.scales_r, j.scale_pld_r,
+                        static_cast<uint8_t*>(j.codes_c), j.code_pld_c, j.scales_c, j.scale_pld_c};
+        quant_tile_kernel<FMT, ROUND, RHT_R, RHT_C, true><<<dim3((unsigned)((pcols + 255) / 256), grid_y(ngrp)), 256, 0, s>>>(
+            x, j.rows, j.cols, j.ld, ngrp, j.qr, j.qc, o);
+        return hipGetLastError();
+    }
+    if constexpr (!kTileAlways<FMT, ROUND, true>) {
+        const dim3 grid((unsigned)((pcols + 16 * kDC - 1) / (16 * kDC)), grid_y((ngrp + 4 * kDB - 1) / (4 * kDB)));
+        quant_dual_kernel<FMT, ROUND, RHT_R, RHT_C><<<grid, 256, 0, s>>>(
+            x, j.rows, j.cols, j.ld, j.qr, j.qc, static_cast<uint8_t*>(j.codes_r), j.code_pld_r, j.scales_r,
+            j.scale_pld_r, static_cast<uint8_t*>(j.codes_c), j.code_pld_c, j.scales_c, j.scale_pld_c);
+    }
     return hipGetLastError();
 }
 
@@ -1426,9 +1611,7 @@ static hipError_t launch_mx_t(const MxQuantJob& j, hipStream_t s) {
         const int64_t n_ct = ((j.transpose ? padded_rows(cols) : cols) + 255) / 256;
         if (n_rt == 0 || n_ct == 0) return hipSuccess;
         const TGroups grp{j.group_off, j.num_groups};
-        // column tiles per workgroup: up to four where that leaves eight workgroups per CU (measured: one tile is 13%
-        // faster than four on 9000 x 1280, sixteen 7% slower than four on 32768 x 5120)
-        const int64_t want = n_rt * n_ct / 2048, chunk = want < 1 ? 1 : want < 4 ? want : 4;
+        const int64_t chunk = group_chunk(n_rt, n_ct);
         const dim3 grid((unsigned)n_rt, (unsigned)((n_ct + chunk - 1) / chunk));
         if (j.transpose)
             mx_tile_grouped_kernel<ROUND, RHT, false><<<grid, 256, 0, s>>>(

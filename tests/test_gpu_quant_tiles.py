@@ -1,0 +1,120 @@
+"""The tile kernels of the quantizers (16 x 256 tiles; 16 M x 256 / M for an RHT block of 16 M) at their edges -- one block,
+tiles cut in rows and columns, panels' padding, a single column, more tiles than one row of the grid -- and the register
+kernels that take large tensors: codes and scales bit for bit the oracle's, buffers prefilled so that padding must be
+written."""
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import ufp4_oracle as O
+from paper_2606_20381_amd import ufp4 as U
+from paper_2606_20381_amd import workloads as WL
+from tests import parity as P
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _need_gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    U.lib()
+
+
+def _x(rows, cols, seed):
+    g = torch.Generator().manual_seed(seed)
+    t = torch.randn(rows, (cols + 7) // 8 * 8, generator=g).bfloat16()
+    return t[:, :cols]  # ld a multiple of 8, a ragged column count
+
+
+def _blank(rows, red, fmt):
+    q = U.empty_qtensor(rows, red, fmt)
+    q.codes.fill_(0xAA)
+    q.scales.fill_(7.0)
+    return q
+
+
+def _padding_is_zero(q):
+    v = q.codes[:, : q.red // 16 * 1024].reshape(q.panels, q.red // 16, 128, 8).permute(0, 2, 1, 3)
+    c = v.reshape(q.panels * 128, -1)[q.rows:]
+    s = q.scales[:, : q.red // 16 * 128].reshape(q.panels, q.red // 16, 128).permute(0, 2, 1)
+    return bool((c == 0).all()) and bool((s.reshape(q.panels * 128, -1)[q.rows:] == 0).all())
+
+
+@pytest.mark.parametrize("shape", [(16, 1), (16, 16), (48, 257), (272, 255), (128, 520), (16 * 70000, 8)])
+@pytest.mark.parametrize("fmt,rounding", [(O.UNIFORM, O.RTNE), (O.UNIFORM, O.SR), (O.E2M1, O.RTNE), (O.E2M1, O.SR)])
+def test_transposed_tiles(shape, fmt, rounding):
+    rows, cols = shape
+    x = _x(rows, cols, rows + cols)
+    xd = torch.empty(rows, (cols + 7) // 8 * 8, dtype=torch.bfloat16, device="cuda")
+    xd[:, :cols] = x.cuda()
+    q = _blank(cols, rows, fmt)
+    fn = U.rht_quantize if fmt == O.UNIFORM else U.e2m1_quantize
+    fn(xd[:, :cols], transpose=True, rht=True, sign_mask=0x1234, rounding=rounding, seed=9, stream_id=1, out=q)
+    torch.cuda.synchronize()
+    bits = WL.bf16_bits(x.contiguous())
+    keep = slice(None) if rows < 10000 else slice(rows - 4096, rows)  # the last blocks of the long tensor
+    if rows < 10000:
+        idx, sc = P.oracle_operand(bits, "cols", fmt, rounding, True, 0x1234, 9, 1)
+        P.assert_codes_equal(*P.gpu_rows(q), idx, sc, fmt, f"{shape}")
+    elif rounding == O.RTNE:  # RTNE does not number its blocks: a slice of the reduction stands alone
+        idx, sc = P.oracle_operand(bits[keep], "cols", fmt, rounding, True, 0x1234, 9, 1)
+        codes, scales = P.gpu_rows(q)
+        P.assert_codes_equal(codes[:, -4096 // 2:], scales[:, -4096 // 16:], idx, sc, fmt, f"{shape}")
+    assert _padding_is_zero(q)
+
+
+@pytest.mark.parametrize("shape", [(16, 16), (144, 272), (272, 240)])
+@pytest.mark.parametrize("fmt,rounding", [(O.UNIFORM, O.RTNE), (O.UNIFORM, O.SR), (O.E2M1, O.RTNE), (O.E2M1, O.SR)])
+def test_dual_tiles(shape, fmt, rounding):
+    rows, cols = shape
+    x = _x(rows, cols, 3 * rows + cols)
+    qr, qc = _blank(rows, cols, fmt), _blank(cols, rows, fmt)
+    U.quantize_dual(x.cuda(), fmt=fmt, sign_mask_rows=0x11, sign_mask_cols=0x22, rounding=rounding, seed=4, stream_rows=2,
+                    stream_cols=5, out_rows=qr, out_cols=qc)
+    torch.cuda.synchronize()
+    bits = WL.bf16_bits(x.contiguous())
+    for q, layout, mask, stream in ((qr, "rows", 0x11, 2), (qc, "cols", 0x22, 5)):
+        idx, sc = P.oracle_operand(bits, layout, fmt, rounding, True, mask, 4, stream)
+        P.assert_codes_equal(*P.gpu_rows(q), idx, sc, fmt, f"{shape} {layout}")
+        assert _padding_is_zero(q)
+
+
+@pytest.mark.parametrize("n", [32, 64, 128])
+@pytest.mark.parametrize("shape", [(1, 1), (3, 130), (2, 33)])  # n-blocks, columns
+@pytest.mark.parametrize("fmt,rounding", [(O.UNIFORM, O.RTNE), (O.UNIFORM, O.SR), (O.E2M1, O.SR)])
+def test_wide_rht_tiles(n, shape, fmt, rounding):
+    rows, cols = shape[0] * n, shape[1]
+    x = _x(rows, cols, n + rows + cols)
+    xd = torch.empty(rows, (cols + 7) // 8 * 8, dtype=torch.bfloat16, device="cuda")
+    xd[:, :cols] = x.cuda()
+    mask = 0x123456789ABCDEF00FEDCBA987654321 & ((1 << n) - 1)
+    q = _blank(cols, rows, fmt)
+    U.quantize_rht_block(xd[:, :cols], fmt, rht_block=n, sign_mask=mask, transpose=True, rounding=rounding, seed=6,
+                         stream_id=3, out=q)
+    torch.cuda.synchronize()
+    a = np.ascontiguousarray(O.bf16_bits_to_f32(WL.bf16_bits(x.contiguous())).T)
+    y = O.rht_rows_n(a, mask, n)
+    idx, sc = O.quantize_rows(y, fmt, rounding, False, 0, 6, 3)
+    P.assert_codes_equal(*P.gpu_rows(q), idx, sc, fmt, f"n={n} {shape}")
+    assert _padding_is_zero(q)
+
+
+@pytest.mark.parametrize("fmt,rounding", [(O.UNIFORM, O.RTNE), (O.UNIFORM, O.SR), (O.E2M1, O.RTNE)])
+def test_large_tensors_keep_the_codes(fmt, rounding):
+    """A tensor past the tiles' size limit (register kernels) against the same blocks taken by the tiles: the first 4096
+    rows quantized by themselves give the same first blocks (the draws are numbered by block and row)."""
+    rows, cols = 16384, 6656  # 109 Mi elements
+    g = torch.Generator(device="cuda").manual_seed(2)
+    x = torch.randn(rows, cols, generator=g, device="cuda").bfloat16()
+    kw = dict(rounding=rounding, seed=8)
+    fn = U.rht_quantize if fmt == O.UNIFORM else U.e2m1_quantize
+    big = fn(x, transpose=True, rht=True, sign_mask=3, stream_id=1, **kw)
+    part = fn(x[:4096], transpose=True, rht=True, sign_mask=3, stream_id=1, **kw)
+    dr, dc = U.quantize_dual(x, fmt=fmt, sign_mask_rows=3, sign_mask_cols=3, stream_rows=0, stream_cols=1, **kw)
+    one = fn(x, rht=True, sign_mask=3, stream_id=0, **kw)
+    torch.cuda.synchronize()
+    assert torch.equal(big.codes[:, : 256 * 1024], part.codes) and torch.equal(big.scales[:, : 256 * 128], part.scales)
+    assert torch.equal(dc.codes, big.codes) and torch.equal(dc.scales, big.scales)
+    assert torch.equal(dr.codes, one.codes) and torch.equal(dr.scales, one.scales)
