@@ -61,7 +61,7 @@ __device__ __forceinline__ float uniform_sr_level(float v, uint32_t u16) {
 // is a power-of-two scaling) it is -((u + f) >> 16), so bits 16-19 of u + f are the two's complement nibble of the
 // negated level. v above 7 (by rounding, at most 7 (1 + 2^-23)) is cut to 7; below -7 the ceiling already gives -7.
 // Four instructions per element (scale, cut, floor, add with a word select of the draw) instead of eight for the
-// comparison on floats: the SR quantizers are VALU bound, and went from 430 to 367 instructions per block.
+// comparison on floats: the SR quantizers are VALU bound, and went from 430 to 383 instructions per block.
 __device__ __forceinline__ uint32_t uniform_sr_neg16(float v, uint32_t u16) {
     const float f = __builtin_fmaxf(v * -65536.0f, -458752.0f);
     int32_t i;
@@ -1078,16 +1078,36 @@ __device__ __forceinline__ void quant_block32_mx(const uint32_t (&w)[16], const 
 // Transposed: consecutive threads take consecutive operand rows (columns of X) of one block, so each of
 // the 16 row loads of a wave reads one contiguous 128-byte run.
 // ------------------------------------------------------------------------------------------------
-constexpr int kStatsThreads = 256;
-constexpr int kStatsMaxGrid = 1024;  // few workgroups: one atomic per field and workgroup
+// What bounds it: vector issue (the fp64 sums), and before that the tail: one atomic per field and workgroup on one cache
+// line, one after the other. 1024 workgroups of 256 threads spent much of their 34 us (8192 x 2048) on them; one
+// workgroup per CU with as many waves issues a quarter of the atomics: 22 us.
+// The sums over magnitudes in fewer fp64 operations and the codes counted by bit planes: 19 us (uniform RTNE without a
+// transform; 32768 x 5120 with the RHT: 159 -> 115 us).
+constexpr int kStatsMinThreads = 256;
+constexpr int kStatsThreads = 1024;  // at most
+constexpr int kStatsMaxGrid = 256;
 
+// Magnitude of a code in units of kLevelUnit<FMT>: 0..7, or twice the E2M1 levels 0 .5 1 1.5 2 3 4 6.
 template <int FMT>
-__device__ __forceinline__ float level_of_nibble(uint32_t nib) {
-    const uint32_t m = nib & 7u;
-    float lv;
-    if constexpr (FMT == kFmtUniform) lv = (float)m;
-    else lv = m <= 4u ? 0.5f * (float)m : (m == 7u ? 6.0f : (float)(m - 2u));  // 0 .5 1 1.5 2 | 3 4 | 6
-    return (nib & 8u) ? -lv : lv;
+__device__ __forceinline__ uint32_t level_of_magnitude(uint32_t m) {
+    if constexpr (FMT == kFmtUniform) return m;
+    else return (0xC8643210u >> (4 * m)) & 15u;
+}
+template <int FMT>
+constexpr double kLevelUnit = FMT == kFmtUniform ? 1.0 : 0.5;
+
+// hist[m] += how many of the sixteen codes have magnitude m: the three magnitude bits of all codes as bit planes, one
+// conjunction and one population count per magnitude.
+__device__ __forceinline__ void count_magnitudes16(uint32_t lo, uint32_t hi, uint32_t (&hist)[8]) {
+    constexpr uint32_t kPlane = 0x11111111u;
+    uint32_t p[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) p[k] = ((lo >> k) & kPlane) | (((hi >> k) & kPlane) << 1);
+    constexpr uint32_t kAll = kPlane | (kPlane << 1);
+#pragma unroll
+    for (int m = 0; m < 8; ++m)
+        hist[m] += __builtin_popcount(((m & 1) ? p[0] : p[0] ^ kAll) & ((m & 2) ? p[1] : p[1] ^ kAll) &
+                                      ((m & 4) ? p[2] : p[2] ^ kAll));
 }
 
 __global__ void stats_zero_kernel(QuantStats* out) {
@@ -1101,39 +1121,54 @@ __global__ void stats_zero_kernel(QuantStats* out) {
 
 template <int FMT, int ROUND, bool RHT, bool TRANS>
 __global__ __launch_bounds__(kStatsThreads) void quant_stats_kernel(const uint16_t* __restrict__ x, int64_t ld,
-                                                                    int64_t qrows, int64_t nb, QuantArgs qa,
+                                                                    int64_t qrows, int64_t nb, int64_t douter,
+                                                                    int64_t dinner, QuantArgs qa,
                                                                     QuantStats* __restrict__ out) {
     double e2 = 0.0, r2 = 0.0, cr = 0.0;
     uint32_t hist[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     const int64_t total = qrows * nb;
-    const int64_t step = (int64_t)gridDim.x * kStatsThreads;
-    for (int64_t id = (int64_t)blockIdx.x * kStatsThreads + threadIdx.x; id < total; id += step) {
-        int64_t r, b;
-        uint32_t w[8];
+    const int64_t step = (int64_t)gridDim.x * blockDim.x;
+    int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    // block id = `outer` * per + `inner`, advanced by step = `douter` * per + `dinner` without a division per block
+    const int64_t per = TRANS ? qrows : nb;
+    int64_t outer = id / per, inner = id - outer * per;
+    uint32_t wn[8];
+    auto fetch = [&](uint32_t (&w)[8]) {
         if constexpr (!TRANS) {
-            r = id / nb;
-            b = id - r * nb;
-            const uint4* src = reinterpret_cast<const uint4*>(x + r * ld + b * kBlock);
+            const uint4* src = reinterpret_cast<const uint4*>(x + outer * ld + inner * kBlock);
             const uint4 v0 = src[0], v1 = src[1];
             w[0] = v0.x; w[1] = v0.y; w[2] = v0.z; w[3] = v0.w;
             w[4] = v1.x; w[5] = v1.y; w[6] = v1.z; w[7] = v1.w;
         } else {
-            b = id / qrows;
-            r = id - b * qrows;
-            const uint16_t* src = x + b * kBlock * ld + r;
+            const uint16_t* src = x + outer * kBlock * ld + inner;
 #pragma unroll
             for (int j = 0; j < 8; ++j) w[j] = (uint32_t)src[(2 * j) * ld] | ((uint32_t)src[(2 * j + 1) * ld] << 16);
         }
+    };
+    if (id < total) fetch(wn);
+    for (; id < total; id += step) {
+        const int64_t r = TRANS ? inner : outer, b = TRANS ? outer : inner;
+        uint32_t w[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) w[j] = wn[j];
+        outer += douter;
+        inner += dinner;
+        if (inner >= per) {
+            inner -= per;
+            ++outer;
+        }
+        if (id + step < total) fetch(wn);  // the next block's words, in flight during this one's arithmetic
         uint32_t lo, hi;
         float sc;
         quant_block16<FMT, ROUND, RHT>(w, qa, (uint32_t)b, (uint32_t)r, lo, hi, sc);
-        // ref = y: a quarter of y' under the RHT, unless y' overflowed (a rotated value past FLT_MAX: then the
-        // fp64 sums give y with 24 significant bits)
+        // The sums run over magnitudes (a code has its value's sign or is zero) and, under the RHT, over y' = 4 y: a
+        // power of two taken out at the end. If y' overflowed (a rotated value past FLT_MAX), the fp64 sums give y with
+        // 24 significant bits.
         float y[16];
         rht16_unscaled<RHT>(w, qa, y);
         double ref[16];
 #pragma unroll
-        for (int i = 0; i < 16; ++i) ref[i] = RHT ? 0.25 * (double)y[i] : (double)y[i];
+        for (int i = 0; i < 16; ++i) ref[i] = __builtin_fabs((double)y[i]);
         if (RHT) {
             float ym = 0.0f;
 #pragma unroll
@@ -1142,25 +1177,29 @@ __global__ __launch_bounds__(kStatsThreads) void quant_stats_kernel(const uint16
                 double t[16];
                 rht16_exact(w, qa, t);
 #pragma unroll
-                for (int i = 0; i < 16; ++i) ref[i] = (double)(float)(t[i] * 0x1p-64) * 0x1p64;
+                for (int i = 0; i < 16; ++i) ref[i] = __builtin_fabs((double)(float)(t[i] * 0x1p-64) * 0x1p66);
             }
         }
-        const double s = (double)sc;
-        uint64_t counts = 0;  // one byte per magnitude code: at most 16 per block
+        const double s = (double)sc * ((RHT ? 4.0 : 1.0) * kLevelUnit<FMT>);
+        double dot = 0.0;
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
-            const uint32_t nib = ((i < 8 ? lo : hi) >> (4 * (i & 7))) & 15u;
-            const double q = (double)level_of_nibble<FMT>(nib) * s;  // a 4-bit level times an fp32 scale: exact
-            const double d = q - ref[i];
+            const uint32_t m = ((i < 8 ? lo : hi) >> (4 * (i & 7))) & 7u;
+            const double lv = (double)level_of_magnitude<FMT>(m);
+            const double d = __builtin_fma(lv, s, -ref[i]);  // a 4-bit level times an fp32 scale is exact
             e2 = __builtin_fma(d, d, e2);
             r2 = __builtin_fma(ref[i], ref[i], r2);
-            cr = __builtin_fma(q, ref[i], cr);
-            counts += 1ull << (8 * (nib & 7u));
+            dot = __builtin_fma(lv, ref[i], dot);
         }
-#pragma unroll
-        for (int m = 0; m < 8; ++m) hist[m] += (uint32_t)(counts >> (8 * m)) & 0xFFu;
+        cr = __builtin_fma(dot, s, cr);
+        count_magnitudes16(lo, hi, hist);
     }
-    // wave sums, then the four waves through LDS, then one atomic per field and workgroup
+    if (RHT) {
+        e2 *= 0.0625;
+        r2 *= 0.0625;
+        cr *= 0.0625;
+    }
+    // wave sums, then the waves through LDS, then one atomic per field and workgroup
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
         e2 += __shfl_xor(e2, o);
@@ -1182,12 +1221,12 @@ __global__ __launch_bounds__(kStatsThreads) void quant_stats_kernel(const uint16
     __syncthreads();
     if (threadIdx.x < 3) {
         double t = 0.0;
-        for (int k = 0; k < kStatsThreads / 64; ++k) t += s_sum[threadIdx.x][k];
+        for (int k = 0; k < (int)blockDim.x / 64; ++k) t += s_sum[threadIdx.x][k];
         atomicAdd(threadIdx.x == 0 ? &out->err2 : (threadIdx.x == 1 ? &out->ref2 : &out->cross), t);
     } else if (threadIdx.x >= 64 && threadIdx.x < 72) {
         const int m = threadIdx.x - 64;
         unsigned long long t = 0;
-        for (int k = 0; k < kStatsThreads / 64; ++k) t += s_hist[m][k];
+        for (int k = 0; k < (int)blockDim.x / 64; ++k) t += s_hist[m][k];
         if (t) atomicAdd(&out->hist[m], t);
     }
 }
@@ -1196,12 +1235,19 @@ template <int FMT, int ROUND, bool RHT>
 static hipError_t launch_stats_t(const StatsJob& j, hipStream_t s) {
     const int64_t nb = j.red / kBlock;
     const int64_t total = j.qrows * nb;
-    const int64_t want = (total + kStatsThreads - 1) / kStatsThreads;
+    // Below one workgroup per CU small workgroups reach more CUs (512 x 512: 8.5 us with 1024 threads, 6.7 with 256).
+    int threads = kStatsMinThreads;
+    while (threads < kStatsThreads && total > (int64_t)kStatsMaxGrid * threads) threads *= 2;
+    const int64_t want = (total + threads - 1) / threads;
     const unsigned grid = (unsigned)(want < kStatsMaxGrid ? want : kStatsMaxGrid);
     if (grid == 0) return hipSuccess;
     const uint16_t* x = static_cast<const uint16_t*>(j.x);
-    if (j.transpose) quant_stats_kernel<FMT, ROUND, RHT, true><<<grid, kStatsThreads, 0, s>>>(x, j.ld, j.qrows, nb, j.qa, j.stats);
-    else quant_stats_kernel<FMT, ROUND, RHT, false><<<grid, kStatsThreads, 0, s>>>(x, j.ld, j.qrows, nb, j.qa, j.stats);
+    const int64_t per = j.transpose ? j.qrows : nb;
+    const int64_t step = (int64_t)grid * threads, douter = step / per, dinner = step % per;
+    if (j.transpose)
+        quant_stats_kernel<FMT, ROUND, RHT, true><<<grid, threads, 0, s>>>(x, j.ld, j.qrows, nb, douter, dinner, j.qa, j.stats);
+    else
+        quant_stats_kernel<FMT, ROUND, RHT, false><<<grid, threads, 0, s>>>(x, j.ld, j.qrows, nb, douter, dinner, j.qa, j.stats);
     return hipGetLastError();
 }
 

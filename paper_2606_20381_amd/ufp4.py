@@ -131,7 +131,7 @@ def _check(status: int, call: str) -> None:
 
 
 # The current stream's handle without building a torch.cuda.Stream for it: that object costs 2.7 us, a third of the host
-# time of a call that launches a kernel of 4 us (8.1 -> 5.5 us per call, 62 -> 43 us for a 256 x 512 x 256 layer step).
+# time of a call that launches a kernel of 4 us (8.1 -> 5.6 us per call, 62 -> 45 us for a 256 x 512 x 256 layer step).
 _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
