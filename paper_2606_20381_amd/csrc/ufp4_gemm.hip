@@ -753,6 +753,9 @@ static GemmKernel pick_kernel(const GemmJob& j) {
         const GemmCost& c = kGemmCost[k];
         double rows = (double)((j.M + c.bm - 1) / c.bm);
         if (j.mode == kGemmRaggedM) rows = (double)j.M / c.bm + 0.5 * j.G;
+        // launch limits: what the large tile's grid can hold must not fail on a smaller tile's (operands of millions of rows)
+        const dim3 grid = gemm_grid(j, c.bm, c.bn);
+        if (k != kTile128 && (grid.y > 65535u || grid.x >= 1u << 22)) continue;
         const double groups = rows * (double)((j.N + c.bn - 1) / c.bn) * (j.mode == kGemmRaggedK ? j.G : 1);
         // the last round counts as partial even when it is full
         const double per_cu = groups / kCUs, rounds = ceil(per_cu / c.resident), full = rounds > 1.0 ? rounds - 1.0 : 0.0;

@@ -420,6 +420,7 @@ static MxKernel pick_mx(const MxGemmJob& j) {
         const double last = c.slope[rest <= 1.0 ? 0 : rest <= 2.0 ? 1 : rest <= 3.0 ? 2 : 3];
         const double us = c.fixed + full * c.again + stages * (full * c.round + last);
         if (k == kMxTile64 && j.nkb >= (int64_t(1) << 20)) continue;  // its load offsets are 32-bit
+        if (k != kMxTile256 && groups >= (double)(1 << 23)) continue;  // 2^32 threads in a one-dimensional grid
         if (k == 0 || us < best_us) {
             best = (MxKernel)k;
             best_us = us;
