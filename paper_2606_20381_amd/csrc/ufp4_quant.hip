@@ -955,12 +955,13 @@ __global__ __launch_bounds__(256) void quant_tile_wide_kernel(const uint16_t* __
 template <int FMT, int ROUND, bool RHT>
 __global__ __launch_bounds__(256) void quant_tile_grouped_kernel(const uint16_t* __restrict__ x, int64_t xrows,
                                                                  int64_t cols, int64_t ld, uint32_t n_ctiles,
-                                                                 uint32_t chunk, TGroups grp, QuantArgs qa, TileOut o) {
+                                                                 uint32_t chunk, int64_t blk0, TGroups grp, QuantArgs qa,
+                                                                 TileOut o) {
     __shared__ int64_t s_off[kMaxGroupsLds + 1];
     __shared__ int64_t s_poff[kMaxGroupsLds + 1];
     __shared__ uint4 tile4[kBlock * kTileWords / 4];
     load_group_offsets<kBlock>(grp, s_off, s_poff);
-    const int64_t P0 = (int64_t)blockIdx.x * kBlock;
+    const int64_t blk = blk0 + blockIdx.x, P0 = blk * kBlock;
     const int g = find_group(s_poff, grp.G, P0);
     const int64_t local0 = P0 - s_poff[g], src0 = s_off[g] + local0;
     int64_t nvalid = s_off[g + 1] - s_off[g] - local0;
@@ -970,7 +971,7 @@ __global__ __launch_bounds__(256) void quant_tile_grouped_kernel(const uint16_t*
     const int64_t src = lr < nvalid ? src0 + lr : -1;
     const uint32_t tc_end = min(n_ctiles, (blockIdx.y + 1) * chunk);
     for (uint32_t tc = blockIdx.y * chunk; tc < tc_end; ++tc) {
-        quant_tile<FMT, ROUND, false, RHT, false>(x, cols, ld, src, 0, blockIdx.x, (int64_t)tc * 256, qa, qa, o, tile4);
+        quant_tile<FMT, ROUND, false, RHT, false>(x, cols, ld, src, 0, blk, (int64_t)tc * 256, qa, qa, o, tile4);
         __syncthreads();  // the tile's column reads before the next tile's writes
     }
 }
@@ -1346,9 +1347,13 @@ static hipError_t launch_cols_grouped(const QuantJob& j, hipStream_t s) {
     if (nblk == 0 || n_ct == 0) return hipSuccess;
     const int64_t chunk = group_chunk(nblk, n_ct);
     const TileOut o{nullptr, 0, nullptr, 0, static_cast<uint8_t*>(j.codes), j.code_pld, j.scales, j.scale_pld};
-    quant_tile_grouped_kernel<FMT, ROUND, RHT><<<dim3((unsigned)nblk, (unsigned)((n_ct + chunk - 1) / chunk)), 256, 0, s>>>(
-        static_cast<const uint16_t*>(j.x), j.xrows, j.qrows, j.ld, (uint32_t)n_ct, (uint32_t)chunk,
-        TGroups{j.group_off, j.num_groups}, j.qa, o);
+    constexpr int64_t kMost = 1 << 22;  // blocks per launch: a grid holds 2^32 threads
+    for (int64_t b = 0; b < nblk; b += kMost) {
+        const dim3 grid((unsigned)(nblk - b < kMost ? nblk - b : kMost), (unsigned)((n_ct + chunk - 1) / chunk));
+        quant_tile_grouped_kernel<FMT, ROUND, RHT><<<grid, 256, 0, s>>>(
+            static_cast<const uint16_t*>(j.x), j.xrows, j.qrows, j.ld, (uint32_t)n_ct, (uint32_t)chunk, b,
+            TGroups{j.group_off, j.num_groups}, j.qa, o);
+    }
     return hipGetLastError();
 }
 
