@@ -1192,7 +1192,17 @@ __global__ __launch_bounds__(kStatsThreads) void quant_stats_kernel(const uint16
             r2 = __builtin_fma(ref[i], ref[i], r2);
             dot = __builtin_fma(lv, ref[i], dot);
         }
-        cr = __builtin_fma(dot, s, cr);
+        // Only a rotated block on the E2M1 grid cut at 2 can have an infinite scale (amax / 2 past the fp32 range); a zero
+        // level times it is NaN, and so is the sum.
+        if (FMT == kFmtE2M1 && RHT && __builtin_expect(!(s <= 0x1p132), 0)) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const uint32_t m = ((i < 8 ? lo : hi) >> (4 * (i & 7))) & 7u;
+                cr = __builtin_fma((double)level_of_magnitude<FMT>(m) * s, ref[i], cr);
+            }
+        } else {
+            cr = __builtin_fma(dot, s, cr);
+        }
         count_magnitudes16(lo, hi, hist);
     }
     if (RHT) {
