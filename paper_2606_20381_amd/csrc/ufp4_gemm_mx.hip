@@ -104,10 +104,9 @@ __device__ __forceinline__ int64_t uniform_i64_mx(int64_t v) {
     return (int64_t)(((uint64_t)hi << 32) | lo);
 }
 
-// Ragged-M: a bound on the number of BM-row tiles over all groups (each group may end in a partial tile).
-template <int BM>
-__host__ __device__ inline int64_t mx_ragged_tiles(const MxGemmJob& j) {
-    return (j.a_rows + BM - 1) / BM + j.G;
+// Tile rows of the grid, for tiles of `bm` rows. Ragged-M: a bound over all groups (each may end in a partial tile).
+__host__ __device__ inline int64_t mx_tile_rows(const MxGemmJob& j, int bm) {
+    return j.mode == kGemmRaggedM ? (j.a_rows + bm - 1) / bm + j.G : (j.M + bm - 1) / bm;
 }
 
 // Ragged-M: the group and local tile of global m-tile t, with the group's padded row start (a multiple of 128)
@@ -191,8 +190,7 @@ __global__ __launch_bounds__(C::kThreads) void gemm_mx_kernel(MxGemmJob j) {
     const int h = lane >> 5, l32 = lane & 31;
     const int wm = (int)((unsigned)wave / C::WN), wn = (int)((unsigned)wave % C::WN);
     int64_t tm, tn;
-    const int64_t gy = j.mode == kGemmRaggedM ? mx_ragged_tiles<BM>(j) : (j.M + BM - 1) / BM;
-    tile_of(blockIdx.x, gy, (j.N + BN - 1) / BN, tm, tn);
+    tile_of(blockIdx.x, mx_tile_rows(j, BM), (j.N + BN - 1) / BN, tm, tn);
     // What the tile covers: A rows from arow0 and B rows from brow0 of the operands, reduction blocks from a_kb0 /
     // b_kb0 (nkb of them), output rows out_row0 .. out_row0 + mrows - 1 (token rows for ragged-M) of the problem at
     // c_base.
@@ -373,10 +371,12 @@ using MxTile256 = MxCfg<4, 2, 2, 4>;  // 256 x 256, 8 waves of 128 x 64, two per
 using MxTile128 = MxCfg<2, 2, 2, 2>;  // 128 x 128, 4 waves, two workgroups per CU
 using MxTile64 = MxCfg<1, 1, 2, 2>;   // 64 x 64, 4 waves, four workgroups per CU
 
+// Workgroups of the (x) grid for square tiles of `bm`.
+static int64_t mx_grid_tiles(const MxGemmJob& j, int bm) { return ((j.N + bm - 1) / bm) * mx_tile_rows(j, bm); }
+
 template <int OUT, class C>
 static hipError_t launch_mx_cfg(const MxGemmJob& j, hipStream_t s) {
-    const int64_t gy = j.mode == kGemmRaggedM ? mx_ragged_tiles<C::BM>(j) : (j.M + C::BM - 1) / C::BM;
-    const int64_t tiles = ((j.N + C::BN - 1) / C::BN) * gy;
+    const int64_t tiles = mx_grid_tiles(j, C::BM);
     if (tiles == 0) return hipSuccess;
     const dim3 grid((unsigned)tiles, j.mode == kGemmRaggedK ? (unsigned)j.G : 1u);
     gemm_mx_kernel<OUT, C><<<grid, C::kThreads, 0, s>>>(j);
@@ -394,13 +394,13 @@ static hipError_t launch_mx_cfg(const MxGemmJob& j, hipStream_t s) {
 // 8192 70.6 -> 33.4, 4096 x 2048 x 2048 24.5 -> 17.8; 4096^3 (45.5; 52.9 on 128 x 128) and larger keep the large tile.
 enum MxKernel { kMxTile256, kMxTile128, kMxTile64, kMxKernels };
 struct MxCost {
-    int tile, resident;
+    int tile, threads, resident;
     double fixed, again, round, slope[4];
 };
 constexpr MxCost kMxCost[kMxKernels] = {
-    {MxTile256::BM, 1, 7.5, 7.3, 1.19, {1.20, 0.0, 0.0, 0.0}},
-    {MxTile128::BM, 2, 5.0, 5.0, 0.66, {0.467, 0.700, 0.0, 0.0}},
-    {MxTile64::BM, 4, 3.5, 2.3, 0.62, {0.262, 0.326, 0.523, 0.647}},
+    {MxTile256::BM, MxTile256::kThreads, 1, 7.5, 7.3, 1.19, {1.20, 0.0, 0.0, 0.0}},
+    {MxTile128::BM, MxTile128::kThreads, 2, 5.0, 5.0, 0.66, {0.467, 0.700, 0.0, 0.0}},
+    {MxTile64::BM, MxTile64::kThreads, 4, 3.5, 2.3, 0.62, {0.262, 0.326, 0.523, 0.647}},
 };
 
 static MxKernel pick_mx(const MxGemmJob& j) {
@@ -420,7 +420,8 @@ static MxKernel pick_mx(const MxGemmJob& j) {
         const double last = c.slope[rest <= 1.0 ? 0 : rest <= 2.0 ? 1 : rest <= 3.0 ? 2 : 3];
         const double us = c.fixed + full * c.again + stages * (full * c.round + last);
         if (k == kMxTile64 && j.nkb >= (int64_t(1) << 20)) continue;  // its load offsets are 32-bit
-        if (k != kMxTile256 && groups >= (double)(1 << 23)) continue;  // 2^32 threads in a one-dimensional grid
+        // a grid holds fewer than 2^32 threads in x: what fits with the large tile must not fail on a smaller tile's grid
+        if (k != kMxTile256 && mx_grid_tiles(j, c.tile) * c.threads > int64_t(UINT32_MAX)) continue;
         if (k == 0 || us < best_us) {
             best = (MxKernel)k;
             best_us = us;
@@ -443,3 +444,17 @@ hipError_t launch_gemm_mx(const MxGemmJob& j, hipStream_t s) {
 }
 
 }  // namespace ufp4
+
+extern "C" int ufp4_plan_gemm_mx(int mode, int64_t M, int64_t N, int64_t red, int32_t G, int64_t a_rows, int64_t* threads_x) {
+    using namespace ufp4;
+    MxGemmJob j{};
+    j.mode = mode;
+    j.M = M;
+    j.N = N;
+    j.nkb = red / 32;
+    j.G = G;
+    j.a_rows = a_rows;
+    const MxKernel k = pick_mx(j);
+    *threads_x = mx_grid_tiles(j, kMxCost[k].tile) * kMxCost[k].threads;
+    return k;
+}

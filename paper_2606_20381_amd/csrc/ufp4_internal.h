@@ -200,3 +200,11 @@ struct GemmJob {
 hipError_t launch_gemm(const GemmJob& job, hipStream_t stream);
 
 }  // namespace ufp4
+
+// The size rules asked from the host, without a GPU: exported for the tests, not part of the interface in include/ufp4.h.
+// They return the kernel that a problem gets, as the enum of its rule.
+extern "C" {
+// `mode` a GemmMode; `red` the reduction (ragged-K: its padded total); `a_rows` the rows stored in A; *threads_x the
+// threads of the grid's x dimension, which a launch limits to 2^32 - 1.
+int ufp4_plan_gemm_mx(int mode, int64_t M, int64_t N, int64_t red, int32_t G, int64_t a_rows, int64_t* threads_x);
+}

@@ -1,0 +1,39 @@
+"""CPU checks of the rules that choose a kernel and its grid by size, through the library's host-only plan queries: launch
+limits (what one kernel's grid can hold must not fail because the rule takes another) and the choices themselves."""
+
+import ctypes
+import os
+
+import pytest
+
+from paper_2606_20381_amd import ufp4 as U
+
+DENSE, RAGGED_M, RAGGED_K = 0, 1, 2
+
+
+@pytest.fixture(scope="module")
+def plan():
+    if not os.path.exists(U.library_path()):
+        pytest.skip("libufp4.so not built")
+    return ctypes.CDLL(U.library_path())
+
+
+def mx_kernel(plan, mode, m, n, red, groups=1, a_rows=None):
+    """(tile, threads of the grid in x) of a power-of-two-scale GEMM; A rows of a ragged-M problem: every group padded."""
+    t = ctypes.c_int64()
+    if a_rows is None:
+        a_rows = (m + 127 * groups) // 128 * 128 if mode == RAGGED_M else m
+    k = plan.ufp4_plan_gemm_mx(mode, *map(ctypes.c_int64, (m, n, red)), ctypes.c_int32(groups), ctypes.c_int64(a_rows),
+                               ctypes.byref(t))
+    return (256, 128, 64)[k], t.value
+
+
+@pytest.mark.parametrize("mode,m,n,red,groups", [
+    (RAGGED_M, 1, 350080, 32, 1024),  # 1024 groups, one token: 3072 tile rows of 64, mostly of empty groups
+    (RAGGED_M, 1000, 200064, 64, 2000),
+    (DENSE, 1 << 20, 1 << 18, 32, 1),  # 2^24 tiles of 128 x 128, 2^26 of 64 x 64
+    (RAGGED_K, 1 << 19, 1 << 17, 32, 2),
+])
+def test_mx_gemm_grids_stay_inside_a_launch(plan, mode, m, n, red, groups):
+    tile, threads = mx_kernel(plan, mode, m, n, red, groups)
+    assert threads < 1 << 32, tile
