@@ -901,16 +901,16 @@ __global__ __launch_bounds__(256) void quant_tile_kernel(const uint16_t* __restr
 // n-block (the sub-blocks of one column) are 64 / M lanes apart in one wave, where rht_wide exchanges their sums.
 template <int FMT, int ROUND, int M>
 __global__ __launch_bounds__(256) void quant_tile_wide_kernel(const uint16_t* __restrict__ x, int64_t cols, int64_t ld,
-                                                              int64_t nnb, QuantArgs qa, uint8_t* __restrict__ codes,
-                                                              int64_t code_pld, float* __restrict__ scales,
-                                                              int64_t scale_pld) {
+                                                              int64_t nnb, int64_t ct0, QuantArgs qa,
+                                                              uint8_t* __restrict__ codes, int64_t code_pld,
+                                                              float* __restrict__ scales, int64_t scale_pld) {
     constexpr int kCols = 256 / M, kW = kCols / 2 + 4, kStep = 64 / M;
     __shared__ uint4 tile4[kBlock * M * kW / 4];
     const uint32_t* const tile = reinterpret_cast<const uint32_t*>(tile4);
     const int t = threadIdx.x;
     const int lr = t % (kBlock * M), lb = t / (kBlock * M);  // this thread's load: 16 columns of a tile row
     const int sub = t % 64 / kStep, c = t / 64 * kStep + t % kStep;  // its block: sub-block and column of the tile
-    const int64_t c0 = (int64_t)blockIdx.x * kCols, gc = c0 + lb * kBlock;
+    const int64_t c0 = (ct0 + blockIdx.x) * kCols, gc = c0 + lb * kBlock;
     for (int64_t nb = blockIdx.y; nb < nnb; nb += gridDim.y) {
         if (nb != blockIdx.y) __syncthreads();  // the last tile's column reads before this one's writes
         uint4 l0 = make_uint4(0, 0, 0, 0), l1 = l0;
@@ -1386,6 +1386,11 @@ static hipError_t launch_cols_t(const QuantJob& j, hipStream_t s) {
     else return launch_cols_regs<FMT, ROUND, RHT, false>(j, s);
 }
 
+// Column tiles (256 / M columns) of a transposed operand after a block-16 M RHT, and how many one launch takes: a grid
+// holds fewer than 2^32 threads in x, and the tiles of n = 128 are 32 columns wide.
+static int64_t wide_col_tiles(int64_t cols, int M) { return (padded_rows(cols) + 256 / M - 1) / (256 / M); }
+constexpr int64_t kWideMostTiles = 1 << 23;
+
 // RHT block of 16 M: the transposed operand (its reduction a multiple of 16 M). Large uniform RTNE tensors at n = 32 keep
 // the register kernel (32768 x 16384: 385 us, 428 on tiles); everywhere else the tiles are faster (8192^2: n = 32 54 -> 50
 // RTNE, 105 -> 60 SR; n = 64 74 -> 57 and 135 -> 70; n = 128 95 -> 83 and 167 -> 89; 4096 x 2048 12-22 -> 9-15).
@@ -1396,11 +1401,16 @@ static hipError_t launch_cols_wide_m(const QuantJob& j, hipStream_t s) {
     if constexpr (FMT == kFmtUniform && ROUND == kRoundRTNE && M == 2) {
         if (j.qrows * j.red > kTileElements) return launch_cols_regs<FMT, ROUND, false, true>(j, s);
     }
-    const dim3 grid((unsigned)((prows + 256 / M - 1) / (256 / M)), grid_y(nnb));
-    quant_tile_wide_kernel<FMT, ROUND, M><<<grid, 256, 0, s>>>(
-        static_cast<const uint16_t*>(j.x), j.qrows, j.ld, nnb, j.qa, static_cast<uint8_t*>(j.codes), j.code_pld, j.scales,
-        j.scale_pld);
-    return hipGetLastError();
+    const int64_t n_ct = wide_col_tiles(j.qrows, M);
+    for (int64_t ct0 = 0; ct0 < n_ct; ct0 += kWideMostTiles) {
+        const dim3 grid((unsigned)(n_ct - ct0 < kWideMostTiles ? n_ct - ct0 : kWideMostTiles), grid_y(nnb));
+        quant_tile_wide_kernel<FMT, ROUND, M><<<grid, 256, 0, s>>>(
+            static_cast<const uint16_t*>(j.x), j.qrows, j.ld, nnb, ct0, j.qa, static_cast<uint8_t*>(j.codes), j.code_pld,
+            j.scales, j.scale_pld);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 template <int FMT, int ROUND>
@@ -1701,3 +1711,8 @@ hipError_t launch_quantize_dual(const DualJob& j, hipStream_t s) {
 int max_groups_quantize() { return kMaxGroupsLds; }
 
 }  // namespace ufp4
+
+extern "C" int64_t ufp4_plan_cols_wide(int rht_block, int64_t cols) {
+    const int64_t n = ufp4::wide_col_tiles(cols, rht_block / 16);
+    return (n < ufp4::kWideMostTiles ? n : ufp4::kWideMostTiles) * 256;
+}

@@ -37,3 +37,10 @@ def mx_kernel(plan, mode, m, n, red, groups=1, a_rows=None):
 def test_mx_gemm_grids_stay_inside_a_launch(plan, mode, m, n, red, groups):
     tile, threads = mx_kernel(plan, mode, m, n, red, groups)
     assert threads < 1 << 32, tile
+
+
+@pytest.mark.parametrize("n", [32, 64, 128])
+@pytest.mark.parametrize("cols", [1, 1 << 29, (1 << 30) - 128, (1 << 31) - 1])
+def test_wide_rht_quantizer_grids_stay_inside_a_launch(plan, n, cols):
+    plan.ufp4_plan_cols_wide.restype = ctypes.c_int64
+    assert 0 < plan.ufp4_plan_cols_wide(n, ctypes.c_int64(cols)) < 1 << 32
