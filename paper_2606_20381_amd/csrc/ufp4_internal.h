@@ -209,4 +209,6 @@ extern "C" {
 int ufp4_plan_gemm_mx(int mode, int64_t M, int64_t N, int64_t red, int32_t G, int64_t a_rows, int64_t* threads_x);
 // Threads in x of the (largest) launch of the transposed quantizer's tile kernel for an RHT block of 32, 64 or 128.
 int64_t ufp4_plan_cols_wide(int rht_block, int64_t cols);
+// Workgroups of a grouped quantizer over `tiles` tiles (mx: power-of-two scales), and the most tiles one of them takes.
+int64_t ufp4_plan_grouped(int mx, int64_t tiles, int64_t* longest_run);
 }

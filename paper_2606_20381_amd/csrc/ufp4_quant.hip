@@ -949,30 +949,39 @@ __global__ __launch_bounds__(256) void quant_tile_wide_kernel(const uint16_t* __
     }
 }
 
-// Grouped reduction: workgroup (x, y) takes block x of the padded token axis and column tiles chunk y .. chunk (y + 1) -
-// 1, so that reading the group offsets is shared by a few tiles. The block's 16 positions lie in one group (group lengths
-// are padded to multiples of 16): rows src0 .. src0 + nvalid - 1 of X and zero padding.
+// Grouped reduction: tile T covers block T / n_ctiles of the padded token axis and column tile T % n_ctiles; a workgroup
+// takes a run of consecutive tiles (grouped_grid), so that reading the group offsets is shared by them. A block's 16
+// positions lie in one group (group lengths are padded to multiples of 16): rows src0 .. src0 + nvalid - 1 of X and zero
+// padding. Bounded to the six waves per SIMD that its LDS allows.
 template <int FMT, int ROUND, bool RHT>
-__global__ __launch_bounds__(256) void quant_tile_grouped_kernel(const uint16_t* __restrict__ x, int64_t xrows,
-                                                                 int64_t cols, int64_t ld, uint32_t n_ctiles,
-                                                                 uint32_t chunk, int64_t blk0, TGroups grp, QuantArgs qa,
-                                                                 TileOut o) {
+__global__ __launch_bounds__(256, 6) void quant_tile_grouped_kernel(const uint16_t* __restrict__ x, int64_t xrows,
+                                                                    int64_t cols, int64_t ld, uint32_t n_ctiles,
+                                                                    uint32_t per, uint32_t more, TGroups grp,
+                                                                    QuantArgs qa, TileOut o) {
     __shared__ int64_t s_off[kMaxGroupsLds + 1];
     __shared__ int64_t s_poff[kMaxGroupsLds + 1];
     __shared__ uint4 tile4[kBlock * kTileWords / 4];
     load_group_offsets<kBlock>(grp, s_off, s_poff);
-    const int64_t blk = blk0 + blockIdx.x, P0 = blk * kBlock;
-    const int g = find_group(s_poff, grp.G, P0);
-    const int64_t local0 = P0 - s_poff[g], src0 = s_off[g] + local0;
-    int64_t nvalid = s_off[g + 1] - s_off[g] - local0;
-    if (src0 + nvalid > xrows) nvalid = xrows - src0;  // offsets beyond X are treated as padding
-    if (src0 < 0 || nvalid < 0) nvalid = 0;
     const int lr = threadIdx.x & 15;
-    const int64_t src = lr < nvalid ? src0 + lr : -1;
-    const uint32_t tc_end = min(n_ctiles, (blockIdx.y + 1) * chunk);
-    for (uint32_t tc = blockIdx.y * chunk; tc < tc_end; ++tc) {
+    const uint32_t T0 = blockIdx.x * per + min(blockIdx.x, more), n = per + (blockIdx.x < more ? 1u : 0u);
+    uint32_t blk = T0 / n_ctiles, tc = T0 - blk * n_ctiles;
+    int64_t src = -1;
+    for (uint32_t i = 0; i < n; ++i) {
+        if (i == 0 || tc == 0) {  // a new block: its group
+            const int64_t P0 = (int64_t)blk * kBlock;
+            const int g = find_group(s_poff, grp.G, P0);
+            const int64_t local0 = P0 - s_poff[g], src0 = s_off[g] + local0;
+            int64_t nvalid = s_off[g + 1] - s_off[g] - local0;
+            if (src0 + nvalid > xrows) nvalid = xrows - src0;  // offsets beyond X are treated as padding
+            if (src0 < 0 || nvalid < 0) nvalid = 0;
+            src = lr < nvalid ? src0 + lr : -1;
+        }
         quant_tile<FMT, ROUND, false, RHT, false>(x, cols, ld, src, 0, blk, (int64_t)tc * 256, qa, qa, o, tile4);
         __syncthreads();  // the tile's column reads before the next tile's writes
+        if (++tc == n_ctiles) {
+            tc = 0;
+            ++blk;
+        }
     }
 }
 
@@ -1332,13 +1341,25 @@ constexpr int64_t kTileElements = 100 << 20;
 template <int FMT, int ROUND, bool DUAL>
 constexpr bool kTileAlways = FMT == kFmtE2M1 ? ROUND == kRoundSR : !DUAL && ROUND == kRoundRTNE;
 
-// Column tiles per workgroup of the grouped kernels, whose group lookup they share: up to four where that leaves eight
-// workgroups per CU (measured on the power-of-two-scale kernel: one tile is 13% faster than four on 9000 x 1280, sixteen
-// 7% slower than four on 32768 x 5120), and as many as keep grid.y in range.
-static int64_t group_chunk(int64_t n_rt, int64_t n_ct) {
-    const int64_t want = n_rt * n_ct / 2048, chunk = want < 1 ? 1 : want < 4 ? want : 4, least = (n_ct + 65534) / 65535;
-    return chunk > least ? chunk : least;
+// Workgroups of the grouped kernels. Each scans the group offsets (up to 1025 of them, two barriers) before its run of
+// tiles, so short runs pay for the scan over and over, and a run longer than its neighbours' keeps the chip waiting. The
+// grid is whole rounds of what the chip holds at once (`resident` workgroups on each of 256 CUs, by the kernels' LDS and
+// registers), as many as keep runs at eight tiles or fewer. Measured, us, one to four column tiles of one block per scan ->
+// now: uniform RTNE, 98304 tokens of 1024 groups, 128 columns 21.0 -> 17.0, 1408 columns of 64 groups 88 -> 82;
+// 400000 x 64 75 -> 54; power-of-two scales 9000 x 1280 of 8 groups 11.2 -> 9.5, 98304 x 2048 133 -> 116; runs of at most
+// four tiles are 1-4% slower, 1536 workgroups of the power-of-two kernels (four to a CU) 4%.
+constexpr int64_t kGroupedResident = 6, kMxGroupedResident = 4;
+struct GroupedGrid {
+    uint32_t workgroups, per, more;  // the first `more` workgroups take per + 1 tiles, the others per
+};
+static GroupedGrid grouped_grid(int64_t tiles, int64_t resident) {
+    const int64_t round = 256 * resident, most = (int64_t(1) << 23) / round;  // a grid holds 2^32 threads
+    int64_t rounds = (tiles + 8 * round - 1) / (8 * round);
+    if (rounds > most) rounds = most;
+    const int64_t wg = rounds * round < tiles ? rounds * round : tiles;
+    return {(uint32_t)wg, (uint32_t)(tiles / wg), (uint32_t)(tiles % wg)};
 }
+constexpr int64_t kMostTiles = int64_t(1) << 31;  // tile numbers are 32 bits: 3 TB of outputs
 
 static unsigned grid_y(int64_t n) { return (unsigned)(n < 65535 ? n : 65535); }
 
@@ -1355,15 +1376,13 @@ template <int FMT, int ROUND, bool RHT>
 static hipError_t launch_cols_grouped(const QuantJob& j, hipStream_t s) {
     const int64_t nblk = j.red / kBlock, n_ct = (padded_rows(j.qrows) + 255) / 256;
     if (nblk == 0 || n_ct == 0) return hipSuccess;
-    const int64_t chunk = group_chunk(nblk, n_ct);
+    const int64_t tiles = nblk * n_ct;
+    if (tiles >= kMostTiles) return hipErrorInvalidValue;
+    const GroupedGrid gg = grouped_grid(tiles, kGroupedResident);
     const TileOut o{nullptr, 0, nullptr, 0, static_cast<uint8_t*>(j.codes), j.code_pld, j.scales, j.scale_pld};
-    constexpr int64_t kMost = 1 << 22;  // blocks per launch: a grid holds 2^32 threads
-    for (int64_t b = 0; b < nblk; b += kMost) {
-        const dim3 grid((unsigned)(nblk - b < kMost ? nblk - b : kMost), (unsigned)((n_ct + chunk - 1) / chunk));
-        quant_tile_grouped_kernel<FMT, ROUND, RHT><<<grid, 256, 0, s>>>(
-            static_cast<const uint16_t*>(j.x), j.xrows, j.qrows, j.ld, (uint32_t)n_ct, (uint32_t)chunk, b,
-            TGroups{j.group_off, j.num_groups}, j.qa, o);
-    }
+    quant_tile_grouped_kernel<FMT, ROUND, RHT><<<gg.workgroups, 256, 0, s>>>(
+        static_cast<const uint16_t*>(j.x), j.xrows, j.qrows, j.ld, (uint32_t)n_ct, gg.per, gg.more,
+        TGroups{j.group_off, j.num_groups}, j.qa, o);
     return hipGetLastError();
 }
 
@@ -1591,8 +1610,8 @@ __global__ __launch_bounds__(256) void mx_tile_kernel(const uint16_t* __restrict
                                            reinterpret_cast<uint32_t*>(tile4));
 }
 
-// Grouped operands: workgroup (tr, y) takes tile row tr of the operand's grouped axis and column tiles
-// chunk y .. chunk (y + 1) - 1, so that reading the group offsets is shared by a few tiles. GROWS
+// Grouped operands: tile T covers tile row T / n_ctiles of the operand's grouped axis and column tile T % n_ctiles; a
+// workgroup takes a run of consecutive tiles (grouped_grid), so that reading the group offsets is shared by them. GROWS
 // (Q_r in grouped-rows form, for the ragged-M GEMMs): operand rows in panels, group g's rows X[off_g ..
 // off_{g+1}) from row P_g = sum_{h<g} pad128(m_h), the rest zero; a tile's 32 rows lie in one group's padded
 // range. Otherwise (Q_c with a grouped reduction, for bwd_dw): the reduction axis is each group's tokens padded
@@ -1600,32 +1619,40 @@ __global__ __launch_bounds__(256) void mx_tile_kernel(const uint16_t* __restrict
 template <int ROUND, bool RHT, bool GROWS>
 __global__ __launch_bounds__(256) void mx_tile_grouped_kernel(const uint16_t* __restrict__ x, int64_t xrows,
                                                               int64_t cols, int64_t ld, uint32_t n_ctiles,
-                                                              uint32_t chunk, int64_t qr_prows, TGroups grp,
+                                                              uint32_t per, uint32_t more, int64_t qr_prows, TGroups grp,
                                                               QuantArgs qa, MxTileOut o) {
     __shared__ int64_t s_off[kMaxGroupsLds + 1];
     __shared__ int64_t s_poff[kMaxGroupsLds + 1];
     __shared__ uint4 tile4[GROWS ? 1 : kMxTileWords / 4];
     load_group_offsets<GROWS ? kPanelRows : kMxBlock>(grp, s_off, s_poff);
     const int lr = threadIdx.x >> 3;
-    const int64_t r0 = (int64_t)blockIdx.x * 32;
-    const int g = find_group(s_poff, grp.G, r0);
-    const int64_t cnt = s_off[g + 1] - s_off[g];
+    const uint32_t T0 = blockIdx.x * per + min(blockIdx.x, more), n = per + (blockIdx.x < more ? 1u : 0u);
+    uint32_t tr = T0 / n_ctiles, tc = T0 - tr * n_ctiles;
     int64_t src = -1;
-    if constexpr (GROWS) {
-        const int64_t local = r0 + lr - s_poff[g], sr = s_off[g] + local;
-        if (local < cnt && sr >= 0 && sr < xrows) src = sr;
-    } else {
-        const int64_t local0 = r0 - s_poff[g], src0 = s_off[g] + local0;
-        int64_t nvalid = cnt - local0;
-        if (src0 + nvalid > xrows) nvalid = xrows - src0;  // offsets beyond X are treated as padding
-        if (src0 < 0 || nvalid < 0) nvalid = 0;
-        if (lr < nvalid) src = src0 + lr;
-    }
-    const uint32_t tc_end = min(n_ctiles, (blockIdx.y + 1) * chunk);
-    for (uint32_t tc = blockIdx.y * chunk; tc < tc_end; ++tc) {
+    for (uint32_t i = 0; i < n; ++i) {
+        const int64_t r0 = (int64_t)tr * 32;
+        if (i == 0 || tc == 0) {  // a new tile row: its group
+            const int g = find_group(s_poff, grp.G, r0);
+            const int64_t cnt = s_off[g + 1] - s_off[g];
+            src = -1;
+            if constexpr (GROWS) {
+                const int64_t local = r0 + lr - s_poff[g], sr = s_off[g] + local;
+                if (local < cnt && sr >= 0 && sr < xrows) src = sr;
+            } else {
+                const int64_t local0 = r0 - s_poff[g], src0 = s_off[g] + local0;
+                int64_t nvalid = cnt - local0;
+                if (src0 + nvalid > xrows) nvalid = xrows - src0;  // offsets beyond X are treated as padding
+                if (src0 < 0 || nvalid < 0) nvalid = 0;
+                if (lr < nvalid) src = src0 + lr;
+            }
+        }
         mx_tile<ROUND, RHT, RHT, GROWS, !GROWS>(x, cols, ld, src, r0 + lr, qr_prows, GROWS ? -1 : r0 / kMxBlock,
                                                 (int64_t)tc * 256, qa, qa, o, reinterpret_cast<uint32_t*>(tile4));
         if constexpr (!GROWS) __syncthreads();  // the tile's column reads before the next tile's writes
+        if (++tc == n_ctiles) {
+            tc = 0;
+            ++tr;
+        }
     }
 }
 
@@ -1682,14 +1709,16 @@ static hipError_t launch_mx_t(const MxQuantJob& j, hipStream_t s) {
         const int64_t n_ct = ((j.transpose ? padded_rows(cols) : cols) + 255) / 256;
         if (n_rt == 0 || n_ct == 0) return hipSuccess;
         const TGroups grp{j.group_off, j.num_groups};
-        const int64_t chunk = group_chunk(n_rt, n_ct);
-        const dim3 grid((unsigned)n_rt, (unsigned)((n_ct + chunk - 1) / chunk));
+        const int64_t tiles = n_rt * n_ct;
+        if (tiles >= kMostTiles) return hipErrorInvalidValue;
+        const GroupedGrid gg = grouped_grid(tiles, kMxGroupedResident);
         if (j.transpose)
-            mx_tile_grouped_kernel<ROUND, RHT, false><<<grid, 256, 0, s>>>(
-                static_cast<const uint16_t*>(j.x), j.xrows, cols, j.ld, (uint32_t)n_ct, (uint32_t)chunk, 0, grp, j.qa, o);
+            mx_tile_grouped_kernel<ROUND, RHT, false><<<gg.workgroups, 256, 0, s>>>(
+                static_cast<const uint16_t*>(j.x), j.xrows, cols, j.ld, (uint32_t)n_ct, gg.per, gg.more, 0, grp, j.qa, o);
         else
-            mx_tile_grouped_kernel<ROUND, RHT, true><<<grid, 256, 0, s>>>(
-                static_cast<const uint16_t*>(j.x), j.xrows, cols, j.ld, (uint32_t)n_ct, (uint32_t)chunk, j.qrows, grp, j.qa, o);
+            mx_tile_grouped_kernel<ROUND, RHT, true><<<gg.workgroups, 256, 0, s>>>(
+                static_cast<const uint16_t*>(j.x), j.xrows, cols, j.ld, (uint32_t)n_ct, gg.per, gg.more, j.qrows, grp,
+                j.qa, o);
         return hipGetLastError();
     }
 }
@@ -1715,4 +1744,10 @@ int max_groups_quantize() { return kMaxGroupsLds; }
 extern "C" int64_t ufp4_plan_cols_wide(int rht_block, int64_t cols) {
     const int64_t n = ufp4::wide_col_tiles(cols, rht_block / 16);
     return (n < ufp4::kWideMostTiles ? n : ufp4::kWideMostTiles) * 256;
+}
+
+extern "C" int64_t ufp4_plan_grouped(int mx, int64_t tiles, int64_t* longest_run) {
+    const ufp4::GroupedGrid g = ufp4::grouped_grid(tiles, mx ? ufp4::kMxGroupedResident : ufp4::kGroupedResident);
+    *longest_run = (int64_t)g.per + (g.more ? 1 : 0);
+    return g.workgroups;
 }

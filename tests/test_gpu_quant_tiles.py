@@ -118,3 +118,68 @@ def test_large_tensors_keep_the_codes(fmt, rounding):
     assert torch.equal(big.codes[:, : 256 * 1024], part.codes) and torch.equal(big.scales[:, : 256 * 128], part.scales)
     assert torch.equal(dc.codes, big.codes) and torch.equal(dc.scales, big.scales)
     assert torch.equal(dr.codes, one.codes) and torch.equal(dr.scales, one.scales)
+
+
+def _grouped_tensor():
+    """30000 tokens of 544 columns (three column tiles) in 300 groups, empty and one-token ones among them: runs of several
+    tiles per workgroup that start and end inside a block's tiles, at blocks and at groups."""
+    g = torch.Generator().manual_seed(12)
+    counts = torch.randint(0, 200, (300,), generator=g).tolist()
+    counts[0] = counts[7] = counts[8] = 0
+    counts[5], counts[-1] = 1, 0
+    counts[-2] += 30000 - sum(counts) if sum(counts) < 30000 else 0
+    x = torch.randn(sum(counts), 544, generator=g).bfloat16().cuda()
+    return x, counts
+
+
+def _pad_groups(x, counts, block):
+    """The rows of x with each group zero-padded to `block`, and the row of the result that every token has."""
+    at, start = [], 0
+    for c in counts:
+        at += range(start, start + c)
+        start += -(-c // block) * block
+    at = torch.tensor(at, device="cuda")
+    out = torch.zeros(start, x.shape[1], dtype=x.dtype, device="cuda")
+    out[at] = x
+    return out, at
+
+
+@pytest.mark.parametrize("fmt,rounding", [(O.UNIFORM, O.RTNE), (O.UNIFORM, O.SR), (O.E2M1, O.RTNE), (O.E2M1, O.SR)])
+@pytest.mark.parametrize("extra", [0, 4800])
+def test_grouped_runs_of_tiles(fmt, rounding, extra):
+    """The grouped transposed operand is the plain one of the zero-padded tensor, blocks past the last group zero."""
+    x, counts = _grouped_tensor()
+    off, red = U.group_offsets(counts, block=16)
+    xp, _ = _pad_groups(x, counts, 16)
+    assert xp.shape[0] == red
+    xp = torch.cat((xp, xp.new_zeros(extra, x.shape[1])))
+    q = _blank(x.shape[1], red + extra, fmt)
+    kw = dict(sign_mask=0x4321, rounding=rounding, seed=5, stream_id=2)
+    U.quantize_grouped_t(x, off, red + extra, fmt=fmt, out=q, **kw)
+    fn = U.rht_quantize if fmt == O.UNIFORM else U.e2m1_quantize
+    want = fn(xp, transpose=True, rht=True, **kw)
+    torch.cuda.synchronize()
+    assert torch.equal(q.codes, want.codes) and torch.equal(q.scales, want.scales)
+
+
+@pytest.mark.parametrize("rounding", [O.RTNE, O.SR])
+def test_mx_grouped_runs_of_tiles(rounding):
+    """Power-of-two scales: the grouped reduction as above, and grouped rows against the plain operand's rows (the draws
+    of a row are numbered by its token)."""
+    x, counts = _grouped_tensor()
+    kw = dict(sign_mask=0x4321, rounding=rounding, seed=5, stream_id=2)
+    off, red = U.group_offsets(counts, block=32)
+    qt = U.mx_quantize_grouped(x, off, red, transpose=True, **kw)
+    want = U.mx_quantize(_pad_groups(x, counts, 32)[0], transpose=True, **kw)
+    torch.cuda.synchronize()
+    assert torch.equal(qt.codes, want.codes) and torch.equal(qt.scales, want.scales)
+    off, rows = U.group_offsets(counts, block=128)
+    qr = U.mx_quantize_grouped(x, off, rows, transpose=False, **kw)
+    plain = U.mx_quantize(x, **kw)
+    at = _pad_groups(x, counts, 128)[1]
+    torch.cuda.synchronize()
+    for got, ref in ((qr.codes_rows(), plain.codes_rows()), (qr.scales_rows(), plain.scales_rows())):
+        assert torch.equal(got[at], ref)
+        rest = torch.ones(rows, dtype=torch.bool, device="cuda")
+        rest[at] = False
+        assert bool((got[rest] == 0).all())

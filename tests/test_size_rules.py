@@ -44,3 +44,17 @@ def test_mx_gemm_grids_stay_inside_a_launch(plan, mode, m, n, red, groups):
 def test_wide_rht_quantizer_grids_stay_inside_a_launch(plan, n, cols):
     plan.ufp4_plan_cols_wide.restype = ctypes.c_int64
     assert 0 < plan.ufp4_plan_cols_wide(n, ctypes.c_int64(cols)) < 1 << 32
+
+
+@pytest.mark.parametrize("mx,resident", [(0, 6), (1, 4)])
+def test_grouped_quantizer_runs(plan, mx, resident):
+    """Every tile in exactly one run, runs that differ by one tile at most, and no scan of the group offsets per tile or
+    two once there is more than one round of workgroups (six or four to a CU)."""
+    plan.ufp4_plan_grouped.restype = ctypes.c_int64
+    longest = ctypes.c_int64()
+    rnd = 256 * resident
+    for tiles in (1, 2, 300, rnd - 1, rnd, rnd + 1, 6144, 8 * rnd, 8 * rnd + 1, 25000, 98305, (1 << 31) - 1):
+        wg = plan.ufp4_plan_grouped(mx, ctypes.c_int64(tiles), ctypes.byref(longest))
+        assert longest.value == -(-tiles // wg) and wg * 256 < 1 << 32
+        assert wg == tiles if tiles <= rnd else wg % rnd == 0
+        assert longest.value >= 4 or tiles < 4 * rnd  # 98304 tokens of 256 columns: 6144 tiles, four to a scan
