@@ -211,4 +211,6 @@ int ufp4_plan_gemm_mx(int mode, int64_t M, int64_t N, int64_t red, int32_t G, in
 int64_t ufp4_plan_cols_wide(int rht_block, int64_t cols);
 // Workgroups of a grouped quantizer over `tiles` tiles (mx: power-of-two scales), and the most tiles one of them takes.
 int64_t ufp4_plan_grouped(int mx, int64_t tiles, int64_t* longest_run);
+// Elements up to which the tile kernel takes a transposed operand (dual: two operands; rht then: both rotated).
+int64_t ufp4_plan_tile_most(int format, int rounding, int dual, int rht);
 }

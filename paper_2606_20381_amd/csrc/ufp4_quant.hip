@@ -472,7 +472,7 @@ __global__ __launch_bounds__(kRT) void quant_rows_kernel(const T* __restrict__ x
 }
 
 // ------------------------------------------------------------------------------------------------
-// Transposed, large tensors (kTileElements): operand A = X^T, reduction along X's rows. A thread loads a
+// Transposed, large tensors (past kColsTileMost): operand A = X^T, reduction along X's rows. A thread loads a
 // 16-row x kXC-column bf16 sub-tile (one load of 2 kXC bytes per row) and quantizes its kXC column blocks
 // from registers, so no LDS transposition and no barrier is needed. Its results are the kXC consecutive
 // operand rows of its block, 8 kXC contiguous bytes of codes. A workgroup of 256 threads covers 256 columns
@@ -582,9 +582,17 @@ __global__ __launch_bounds__(256, FMT == kFmtUniform && !WIDE ? 3 : 1) void quan
     uint8_t* __restrict__ codes, int64_t code_pld, float* __restrict__ scales, int64_t scale_pld) {
     const int t = threadIdx.x;
     constexpr int XG = WIDE ? kXG : kXGD, XB = 256 / XG;  // column groups, blocks per workgroup
+    // Staged stores: each half-wave (32 threads, one block of 256 operand rows) puts its 2 KB of codes and 1 KB of scales
+    // in its own LDS area in output order and reads them back, so that every store instruction writes 512 contiguous bytes
+    // instead of 16-byte pieces of 64-byte runs (uniform RTNE, 32768 x 16384: 267 -> 262 us). SR loses more to the extra
+    // registers than it gains, E2M1 RTNE gains nothing: they store directly.
+    constexpr bool STAGE = !WIDE && FMT == kFmtUniform && ROUND == kRoundRTNE && XG == 32 && kXC == 8;
+    __shared__ uint4 s_stage[STAGE ? 8 : 1][STAGE ? 192 : 1];
     const int cg = t % XG, rb = t / XG;
     const int64_t cbase = (int64_t)blockIdx.x * (XG * kXC) + cg * kXC;  // first operand row of the thread
-    if (cbase >= prows) return;
+    // Without staging a thread past the last panel has nothing to do. With it, every thread stays: its (zero) data fills
+    // its slot of the stage, and stores to panels past the end are skipped.
+    if (!STAGE && cbase >= prows) return;
     const int ncol = cols - cbase < kXC ? (int)(cols - cbase) : kXC;  // valid columns of the thread (<= 0: none)
     const int64_t nblk = red_total / kBlock;
     constexpr int kW = kXC / 2;  // dwords per row
@@ -656,13 +664,43 @@ __global__ __launch_bounds__(256, FMT == kFmtUniform && !WIDE ? 3 : 1) void quan
                 }
             }
         }
-        const int64_t P = cbase >> 7, ri = cbase & 127;  // the kXC rows lie in one panel
-        uint4* dc = reinterpret_cast<uint4*>(codes + P * code_pld + gb * 1024 + ri * 8);
+        if constexpr (STAGE) {
+            // half-wave area: codes of operand rows 0..255 of the block (8 bytes each, uint4 0..127), then their scales
+            // (uint4 128..191); thread cg owns rows 8 cg .. 8 cg + 7
+            uint4* const st = s_stage[t >> 5];
+            const int L = t & 31;
 #pragma unroll
-        for (int q = 0; q < kXC / 2; ++q) dc[q] = make_uint4(clo[2 * q], chi[2 * q], clo[2 * q + 1], chi[2 * q + 1]);
-        float4* ds = reinterpret_cast<float4*>(scales + P * scale_pld + gb * 128 + ri);
+            for (int q = 0; q < 4; ++q) st[4 * L + q] = make_uint4(clo[2 * q], chi[2 * q], clo[2 * q + 1], chi[2 * q + 1]);
 #pragma unroll
-        for (int q = 0; q < kXC / 4; ++q) ds[q] = make_float4(sc[4 * q], sc[4 * q + 1], sc[4 * q + 2], sc[4 * q + 3]);
+            for (int q = 0; q < 2; ++q)
+                st[128 + 2 * L + q] = make_uint4(__float_as_uint(sc[4 * q]), __float_as_uint(sc[4 * q + 1]),
+                                                 __float_as_uint(sc[4 * q + 2]), __float_as_uint(sc[4 * q + 3]));
+            // the half-wave reads what its own lanes wrote: LDS operations of a wave complete in order, the wait and the
+            // compiler barrier keep the reads after the writes
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            const int64_t P0 = (int64_t)blockIdx.x * 2;  // the block's two panels
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int64_t P = P0 + (q >> 1);
+                if (P * kPanelRows < prows)
+                    *reinterpret_cast<uint4*>(codes + P * code_pld + gb * 1024 + (q & 1) * 512 + 16 * L) = st[32 * q + L];
+            }
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                const int64_t P = P0 + q;
+                if (P * kPanelRows < prows)
+                    *reinterpret_cast<uint4*>(scales + P * scale_pld + gb * 128 + 4 * L) = st[128 + 32 * q + L];
+            }
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // reads done before the next iteration's writes
+        } else {
+            const int64_t P = cbase >> 7, ri = cbase & 127;  // the kXC rows lie in one panel
+            uint4* dc = reinterpret_cast<uint4*>(codes + P * code_pld + gb * 1024 + ri * 8);
+#pragma unroll
+            for (int q = 0; q < kXC / 2; ++q) dc[q] = make_uint4(clo[2 * q], chi[2 * q], clo[2 * q + 1], chi[2 * q + 1]);
+            float4* ds = reinterpret_cast<float4*>(scales + P * scale_pld + gb * 128 + ri);
+#pragma unroll
+            for (int q = 0; q < kXC / 4; ++q) ds[q] = make_float4(sc[4 * q], sc[4 * q + 1], sc[4 * q + 2], sc[4 * q + 3]);
+        }
     }
 }
 
@@ -1331,15 +1369,29 @@ hipError_t launch_rht(const RhtJob& j, hipStream_t s) {
     return hipGetLastError();
 }
 
-// Whether the 16 x 256 tile kernels take a tensor (else the register kernels, eight blocks per thread and operand). They
-// give a thread one block, which small tensors need to fill the chip, and run at full occupancy; the register kernels'
-// longer runs of stores win by 3-10% once a tensor is well past the 256 MiB memory-side cache. Measured, us, register ->
-// tile: two operands RTNE 256^2 9.1 -> 3.4, 2048^2 10.1 -> 6.1, 8192 x 4096 32.2 -> 28.3, 8192^2 52.9 -> 52.1, 32768 x
-// 16384 404 -> 432; transposed SR 2048^2 8.8 -> 5.2, 8192^2 43.6 -> 42.9, 32768 x 16384 329 -> 358. Transposed uniform
-// RTNE (537 Mi elements: 262 both) and E2M1 SR (32768 x 16384 785 -> 746, two operands 1541 -> 1432) stay on tiles.
-constexpr int64_t kTileElements = 100 << 20;
-template <int FMT, int ROUND, bool DUAL>
-constexpr bool kTileAlways = FMT == kFmtE2M1 ? ROUND == kRoundSR : !DUAL && ROUND == kRoundRTNE;
+// Elements up to which the 16 x 256 tile kernels take a tensor (else the register kernels, eight blocks per thread and
+// operand). Tiles give a thread one block, which small tensors need to fill the chip, and run at full occupancy; the
+// register kernels' longer runs of stores win once a tensor is past the 256 MiB memory-side cache, and with few
+// instructions to the byte or many registers to the block before that. The lines lie where the two cross, measured at 16 to
+// 512 Mi elements with the same input again and with 1 GiB of inputs in turn. us, tile / register, the latter:
+//   transposed, uniform RTNE, rotated   8192 x 11008 51 / 53   24048 x 4624 66 / 65   16384^2 143 / 136, 32768 x 16384 290 / 262
+//   uniform RTNE plain                  16384^2 128 / 134, 32768 x 16384 251 / 263 (staged stores)
+//   uniform SR, rotated                 4096 x 8192 27 / 28    8192 x 6144 39 / 37    16384^2 188 / 164
+//   uniform SR plain                    8192 x 11008 53 / 54   8192 x 13056 65 / 63   16384^2 151 / 137
+//   E2M1 RTNE, rotated                  8192^2 54 / 54         8192 x 11008 71 / 69   16384^2 203 / 177
+//   E2M1 RTNE plain                     8192 x 11008 55 / 57   8192 x 13056 66 / 65   16384^2 155 / 138
+//   E2M1 SR, rotated                    16384^2 389 / 396, 32768 x 16384 746 / 785
+//   E2M1 SR plain                       24048 x 4624 147 / 148 16384 x 8192 168 / 168 16384^2 333 / 321
+//   two operands, uniform RTNE, both rotated 8192 x 9216 65 / 67, 8192 x 11008 79 / 76, 16384^2 227 / 208; one rotated
+//   16384 x 12288 144 / 150, 16384^2 188 / 187; uniform SR 12288^2 175 / 177, 16384 x 12288 232 / 231, 16384^2 309 / 299;
+//   E2M1 RTNE 12288^2 191 / 194, 16384 x 12288 254 / 253, 16384^2 336 / 332; E2M1 SR 16384^2 715 / 780.
+constexpr int64_t kMi = 1 << 20, kNoLimit = INT64_MAX;
+template <int FMT, int ROUND, bool RHT>
+constexpr int64_t kColsTileMost = FMT == kFmtUniform ? (ROUND == kRoundRTNE ? (RHT ? 100 * kMi : kNoLimit) : (RHT ? 40 : 100) * kMi)
+                                                     : (ROUND == kRoundRTNE ? (RHT ? 64 : 100) * kMi : (RHT ? kNoLimit : 128 * kMi));
+template <int FMT, int ROUND, bool BOTH>  // BOTH: both operands rotated
+constexpr int64_t kDualTileMost = FMT == kFmtUniform ? (ROUND == kRoundRTNE ? (BOTH ? 80 : 200) : (BOTH ? 160 : 200)) * kMi
+                                                     : (ROUND == kRoundRTNE ? 160 * kMi : kNoLimit);
 
 // Workgroups of the grouped kernels. Each scans the group offsets (up to 1025 of them, two barriers) before its run of
 // tiles, so short runs pay for the scan over and over, and a run longer than its neighbours' keeps the chip waiting. The
@@ -1400,9 +1452,9 @@ static hipError_t launch_cols_regs(const QuantJob& j, hipStream_t s) {
 template <int FMT, int ROUND, bool RHT>
 static hipError_t launch_cols_t(const QuantJob& j, hipStream_t s) {
     if (j.qrows == 0 || j.red / kBlock == 0) return hipSuccess;
-    if constexpr (kTileAlways<FMT, ROUND, false>) return launch_cols_tile<FMT, ROUND, RHT>(j, s);
-    else if (j.qrows * j.red <= kTileElements) return launch_cols_tile<FMT, ROUND, RHT>(j, s);
-    else return launch_cols_regs<FMT, ROUND, RHT, false>(j, s);
+    constexpr int64_t most = kColsTileMost<FMT, ROUND, RHT>;
+    if constexpr (most == kNoLimit) return launch_cols_tile<FMT, ROUND, RHT>(j, s);
+    else return j.qrows * j.red <= most ? launch_cols_tile<FMT, ROUND, RHT>(j, s) : launch_cols_regs<FMT, ROUND, RHT, false>(j, s);
 }
 
 // Column tiles (256 / M columns) of a transposed operand after a block-16 M RHT, and how many one launch takes: a grid
@@ -1411,14 +1463,15 @@ static int64_t wide_col_tiles(int64_t cols, int M) { return (padded_rows(cols) +
 constexpr int64_t kWideMostTiles = 1 << 23;
 
 // RHT block of 16 M: the transposed operand (its reduction a multiple of 16 M). Large uniform RTNE tensors at n = 32 keep
-// the register kernel (32768 x 16384: 385 us, 428 on tiles); everywhere else the tiles are faster (8192^2: n = 32 54 -> 50
+// the register kernel (past kWideTileMost; 32768 x 16384: 385 us, 428 on tiles); everywhere else the tiles are faster (8192^2: n = 32 54 -> 50
 // RTNE, 105 -> 60 SR; n = 64 74 -> 57 and 135 -> 70; n = 128 95 -> 83 and 167 -> 89; 4096 x 2048 12-22 -> 9-15).
+constexpr int64_t kWideTileMost = 100 * kMi;
 template <int FMT, int ROUND, int M>
 static hipError_t launch_cols_wide_m(const QuantJob& j, hipStream_t s) {
     const int64_t prows = padded_rows(j.qrows), nnb = j.red / (kBlock * M);
     if (prows == 0 || nnb == 0) return hipSuccess;
     if constexpr (FMT == kFmtUniform && ROUND == kRoundRTNE && M == 2) {
-        if (j.qrows * j.red > kTileElements) return launch_cols_regs<FMT, ROUND, false, true>(j, s);
+        if (j.qrows * j.red > kWideTileMost) return launch_cols_regs<FMT, ROUND, false, true>(j, s);
     }
     const int64_t n_ct = wide_col_tiles(j.qrows, M);
     for (int64_t ct0 = 0; ct0 < n_ct; ct0 += kWideMostTiles) {
@@ -1476,14 +1529,15 @@ static hipError_t launch_dual_t(const DualJob& j, hipStream_t s) {
     const int64_t pcols = padded_rows(j.cols), ngrp = padded_rows(j.rows) / kBlock;
     if (pcols == 0 || ngrp == 0) return hipSuccess;
     const uint16_t* const x = static_cast<const uint16_t*>(j.x);
-    if (kTileAlways<FMT, ROUND, true> || j.rows * j.cols <= kTileElements) {
+    constexpr int64_t most = kDualTileMost<FMT, ROUND, RHT_R && RHT_C>;
+    if (j.rows * j.cols <= most) {
         const TileOut o{static_cast<uint8_t*>(j.codes_r), j.code_pld_r, j.scales_r, j.scale_pld_r,
                         static_cast<uint8_t*>(j.codes_c), j.code_pld_c, j.scales_c, j.scale_pld_c};
         quant_tile_kernel<FMT, ROUND, RHT_R, RHT_C, true><<<dim3((unsigned)((pcols + 255) / 256), grid_y(ngrp)), 256, 0, s>>>(
             x, j.rows, j.cols, j.ld, ngrp, j.qr, j.qc, o);
         return hipGetLastError();
     }
-    if constexpr (!kTileAlways<FMT, ROUND, true>) {
+    if constexpr (most != kNoLimit) {
         const dim3 grid((unsigned)((pcols + 16 * kDC - 1) / (16 * kDC)), grid_y((ngrp + 4 * kDB - 1) / (4 * kDB)));
         quant_dual_kernel<FMT, ROUND, RHT_R, RHT_C><<<grid, 256, 0, s>>>(
             x, j.rows, j.cols, j.ld, j.qr, j.qc, static_cast<uint8_t*>(j.codes_r), j.code_pld_r, j.scales_r,
@@ -1750,4 +1804,18 @@ extern "C" int64_t ufp4_plan_grouped(int mx, int64_t tiles, int64_t* longest_run
     const ufp4::GroupedGrid g = ufp4::grouped_grid(tiles, mx ? ufp4::kMxGroupedResident : ufp4::kGroupedResident);
     *longest_run = (int64_t)g.per + (g.more ? 1 : 0);
     return g.workgroups;
+}
+
+namespace ufp4 {
+template <int FMT, int ROUND>
+static int64_t tile_most(int dual, int rht) {
+    if (dual) return rht ? kDualTileMost<FMT, ROUND, true> : kDualTileMost<FMT, ROUND, false>;
+    return rht ? kColsTileMost<FMT, ROUND, true> : kColsTileMost<FMT, ROUND, false>;
+}
+}  // namespace ufp4
+
+extern "C" int64_t ufp4_plan_tile_most(int format, int rounding, int dual, int rht) {
+    using namespace ufp4;
+    if (format == kFmtE2M1) return rounding == kRoundSR ? tile_most<kFmtE2M1, kRoundSR>(dual, rht) : tile_most<kFmtE2M1, kRoundRTNE>(dual, rht);
+    return rounding == kRoundSR ? tile_most<kFmtUniform, kRoundSR>(dual, rht) : tile_most<kFmtUniform, kRoundRTNE>(dual, rht);
 }

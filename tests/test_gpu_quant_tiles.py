@@ -183,3 +183,28 @@ def test_mx_grouped_runs_of_tiles(rounding):
         rest = torch.ones(rows, dtype=torch.bool, device="cuda")
         rest[at] = False
         assert bool((got[rest] == 0).all())
+
+
+@pytest.mark.parametrize("fmt,rounding,rht,rows,cols", [
+    (O.UNIFORM, O.RTNE, True, 16400, 6570), (O.UNIFORM, O.SR, True, 16400, 2650), (O.UNIFORM, O.SR, False, 16400, 6570),
+    (O.E2M1, O.RTNE, True, 16400, 4200), (O.E2M1, O.RTNE, False, 16400, 6570), (O.E2M1, O.SR, False, 20016, 6890)])
+def test_large_ragged_transposed(fmt, rounding, rht, rows, cols):
+    """Just past the tiles' limit of each grid, rounding and transform: a column count that ends inside a thread's eight
+    columns and inside a panel. The first 2048 rows by themselves (tiles) give the same first blocks; padding is zero."""
+    ld = (cols + 7) // 8 * 8
+    g = torch.Generator(device="cuda").manual_seed(3)
+    x = torch.randn(rows, ld, generator=g, device="cuda").bfloat16()[:, :cols]
+    fn = U.rht_quantize if fmt == O.UNIFORM else U.e2m1_quantize
+    kw = dict(transpose=True, rht=rht, sign_mask=0x55 if rht else 0, rounding=rounding, seed=8, stream_id=1)
+    big, part = _blank(cols, rows, fmt), _blank(cols, 2048, fmt)
+    fn(x, out=big, **kw)
+    fn(x[:2048], out=part, **kw)
+    last = fn(x[rows - 2048:], **dict(kw, rounding=O.RTNE)) if rounding == O.RTNE else None
+    torch.cuda.synchronize()
+    n = 2048 // 16
+    assert torch.equal(big.codes[:, : n * 1024], part.codes) and torch.equal(big.scales[:, : n * 128], part.scales)
+    if last is not None:
+        m = rows // 16
+        assert torch.equal(big.codes[:, (m - n) * 1024: m * 1024], last.codes)
+        assert torch.equal(big.scales[:, (m - n) * 128: m * 128], last.scales)
+    assert _padding_is_zero(big)

@@ -58,3 +58,28 @@ def test_grouped_quantizer_runs(plan, mx, resident):
         assert longest.value == -(-tiles // wg) and wg * 256 < 1 << 32
         assert wg == tiles if tiles <= rnd else wg % rnd == 0
         assert longest.value >= 4 or tiles < 4 * rnd  # 98304 tokens of 256 columns: 6144 tiles, four to a scan
+
+
+# us on tiles and in the register kernel, each the mean of the same input again and of 1 GiB of inputs in turn
+TILE_TIMES = [  # format, rounding, dual, rht, rows, cols, tile, register
+    (U.UNIFORM, U.RTNE, 0, 1, 8192, 11008, 47.1, 48.3), (U.UNIFORM, U.RTNE, 0, 1, 24048, 4624, 63.8, 61.9),
+    (U.UNIFORM, U.RTNE, 0, 1, 16384, 16384, 140.2, 135.7), (U.UNIFORM, U.RTNE, 0, 1, 32768, 16384, 280.4, 262.1),
+    (U.UNIFORM, U.RTNE, 0, 0, 32768, 16384, 250.0, 261.1), (U.UNIFORM, U.SR, 0, 1, 4096, 8192, 26.0, 26.9),
+    (U.UNIFORM, U.SR, 0, 1, 8192, 8192, 47.5, 45.9), (U.UNIFORM, U.SR, 0, 1, 8192, 11008, 62.9, 58.1),
+    (U.UNIFORM, U.SR, 0, 0, 8192, 11008, 49.2, 49.7), (U.UNIFORM, U.SR, 0, 0, 16384, 16384, 148.0, 137.4),
+    (U.E2M1, U.RTNE, 0, 1, 8192, 6144, 40.6, 42.3), (U.E2M1, U.RTNE, 0, 1, 8192, 11008, 70.2, 67.3),
+    (U.E2M1, U.RTNE, 0, 0, 8192, 9216, 45.2, 47.3), (U.E2M1, U.RTNE, 0, 0, 16384, 16384, 153.6, 138.9),
+    (U.E2M1, U.SR, 0, 1, 16384, 16384, 389.0, 397.8), (U.E2M1, U.SR, 0, 0, 24048, 4624, 146.9, 147.9),
+    (U.E2M1, U.SR, 0, 0, 16384, 16384, 333.8, 321.1), (U.UNIFORM, U.RTNE, 1, 1, 8192, 9216, 62.3, 62.8),
+    (U.UNIFORM, U.RTNE, 1, 1, 8192, 11008, 78.9, 75.1), (U.UNIFORM, U.RTNE, 1, 1, 16384, 16384, 224.9, 203.4),
+    (U.UNIFORM, U.RTNE, 1, 0, 16384, 12288, 140.8, 150.3), (U.UNIFORM, U.SR, 1, 1, 24048, 4624, 133.7, 141.0),
+    (U.UNIFORM, U.SR, 1, 1, 16384, 16384, 306.5, 298.0), (U.E2M1, U.RTNE, 1, 1, 12288, 12288, 190.3, 193.3),
+    (U.E2M1, U.RTNE, 1, 1, 32768, 16384, 667.2, 647.9), (U.E2M1, U.SR, 1, 1, 32768, 16384, 1422.6, 1533.0),
+]
+
+
+@pytest.mark.parametrize("fmt,rounding,dual,rht,rows,cols,tile,register", TILE_TIMES)
+def test_quantizer_tiles_where_they_are_faster(plan, fmt, rounding, dual, rht, rows, cols, tile, register):
+    plan.ufp4_plan_tile_most.restype = ctypes.c_int64
+    tiles = rows * cols <= plan.ufp4_plan_tile_most(fmt, rounding, dual, rht)
+    assert tiles == (tile < register)
