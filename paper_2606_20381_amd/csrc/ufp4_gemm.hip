@@ -743,25 +743,32 @@ constexpr GemmCost kGemmCost[kGemmKernels] = {
     {Direct64::BM, Direct64::BN, 3, 6.0, 4.5, 0.188, {0.108, 0.129, 0.188}},
 };
 
+// Ragged-M: every workgroup first finds its group (a prefix sum over the offsets and two barriers before any load), and
+// so do those that find none. Per workgroup and CU, measured on 2 to 256 groups. Without it, and with half a tile per group
+// counted, small tiles were taken for many small groups, us, 128 x 128 / then picked / now: 1273 tokens of 128 groups,
+// 5248 x 256 122 / 165 / 122; 600 of 256, 1536 x 256 66 / 96 / 66; one group of 3124, 1280 x 1152 35 / 44 / 28.
+constexpr double kLookupUs = 1.0;
+
 static GemmKernel pick_kernel(const GemmJob& j) {
     constexpr double kCUs = 256.0;
-    // ragged-K: an average group; ragged-M: half a tile lost per group
-    const double blocks = j.mode == kGemmRaggedK ? (double)j.red_total / 16.0 / j.G : (double)j.nkb;
+    const double blocks = j.mode == kGemmRaggedK ? (double)j.red_total / 16.0 / j.G : (double)j.nkb;  // an average group
     GemmKernel best = kTile128;
     double best_us = 0.0;
     for (int k = 0; k < kGemmKernels; ++k) {
         const GemmCost& c = kGemmCost[k];
-        double rows = (double)((j.M + c.bm - 1) / c.bm);
-        if (j.mode == kGemmRaggedM) rows = (double)j.M / c.bm + 0.5 * j.G;
         // launch limits: what the large tile's grid can hold must not fail on a smaller tile's (operands of millions of rows)
         const dim3 grid = gemm_grid(j, c.bm, c.bn);
         if (k != kTile128 && (grid.y > 65535u || grid.x >= 1u << 22)) continue;
-        const double groups = rows * (double)((j.N + c.bn - 1) / c.bn) * (j.mode == kGemmRaggedK ? j.G : 1);
+        // Ragged-M: all workgroups of the grid count, a tile row for each group's remainder among them. Those without rows
+        // are short, but which XCD they fall to is not known here: 250 tiles and 10 empty workgroups are 33 on some of
+        // the 8 XCDs of 32 CUs, a second round for the kernel that runs one per CU.
+        const double per_cu = (double)grid.x * grid.y * grid.z / kCUs;
         // the last round counts as partial even when it is full
-        const double per_cu = groups / kCUs, rounds = ceil(per_cu / c.resident), full = rounds > 1.0 ? rounds - 1.0 : 0.0;
+        const double rounds = ceil(per_cu / c.resident), full = rounds > 1.0 ? rounds - 1.0 : 0.0;
         const double rest = per_cu - full * c.resident;
         const double last = c.slope[rest <= 1.0 ? 0 : rest <= 2.0 ? 1 : 2];
         double us = c.fixed + full * c.again + blocks * (full * c.round + last);
+        if (j.mode == kGemmRaggedM) us += kLookupUs * per_cu;
         if (k == kTile128) us *= 0.96;  // the estimates' spread: within it the large tile stays
         if (k == 0 || us < best_us) {
             best = (GemmKernel)k;
@@ -790,3 +797,15 @@ hipError_t launch_gemm(const GemmJob& j, hipStream_t s) {
 }
 
 }  // namespace ufp4
+
+extern "C" int ufp4_plan_gemm(int mode, int format, int64_t M, int64_t N, int64_t red, int32_t G) {
+    ufp4::GemmJob j{};
+    j.mode = mode;
+    j.format = format;
+    j.M = M;
+    j.N = N;
+    j.nkb = red / 16;
+    j.red_total = red;
+    j.G = G;
+    return ufp4::pick_kernel(j);
+}

@@ -206,6 +206,7 @@ hipError_t launch_gemm(const GemmJob& job, hipStream_t stream);
 extern "C" {
 // `mode` a GemmMode; `red` the reduction (ragged-K: its padded total); `a_rows` the rows stored in A; *threads_x the
 // threads of the grid's x dimension, which a launch limits to 2^32 - 1.
+int ufp4_plan_gemm(int mode, int format, int64_t M, int64_t N, int64_t red, int32_t G);
 int ufp4_plan_gemm_mx(int mode, int64_t M, int64_t N, int64_t red, int32_t G, int64_t a_rows, int64_t* threads_x);
 // Threads in x of the (largest) launch of the transposed quantizer's tile kernel for an RHT block of 32, 64 or 128.
 int64_t ufp4_plan_cols_wide(int rht_block, int64_t cols);

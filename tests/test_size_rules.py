@@ -28,6 +28,38 @@ def mx_kernel(plan, mode, m, n, red, groups=1, a_rows=None):
     return (256, 128, 64)[k], t.value
 
 
+KERNELS = ("128x128", "128x128 in two K groups", "128x64", "32x32", "64x64")
+
+
+def gemm_kernel(plan, mode, fmt, m, n, red, groups=1):
+    return plan.ufp4_plan_gemm(mode, fmt, *map(ctypes.c_int64, (m, n, red)), ctypes.c_int32(groups))
+
+
+# us of each of KERNELS
+RAGGED_M_TIMES = [  # format, tokens, columns, reduction, groups
+    (U.UNIFORM, 1273, 5248, 256, 128, (122.0, 209.9, 132.6, 165.1, 124.3)),
+    (U.UNIFORM, 600, 1536, 256, 256, (66.2, 121.3, 78.8, 96.1, 71.3)),
+    (U.UNIFORM, 3124, 1280, 1152, 1, (34.8, 44.2, 31.7, 38.8, 28.1)),
+    (U.UNIFORM, 9827, 384, 1024, 16, (34.4, 42.7, 30.4, 40.3, 27.0)),
+    (U.UNIFORM, 6652, 640, 384, 32, (17.7, 24.3, 21.3, 32.2, 20.8)),
+    (U.UNIFORM, 2098, 2304, 1536, 8, (46.5, 55.0, 57.0, 59.4, 46.0)),
+    (U.E2M1, 10780, 256, 384, 32, (12.7, 13.5, 12.6, 22.1, 16.4)),
+    (U.E2M1, 725, 1152, 256, 128, (29.0, 45.3, 39.7, 35.2, 29.3)),
+    (U.E2M1, 18189, 3712, 512, 64, (209.0, 316.9, 281.9, 481.7, 266.6)),
+]
+
+
+def _assert_no_slower_than_the_large_tile(plan, mode, fmt, m, n, red, groups, us):
+    """The kernel taken is within 4% of the 128 x 128 one (the spread that the rule grants it) or faster."""
+    k = gemm_kernel(plan, mode, fmt, m, n, red, groups)
+    assert us[k] <= 1.04 * us[0], KERNELS[k]
+
+
+@pytest.mark.parametrize("fmt,m,n,red,groups,us", RAGGED_M_TIMES)
+def test_ragged_m_kernels(plan, fmt, m, n, red, groups, us):
+    _assert_no_slower_than_the_large_tile(plan, RAGGED_M, fmt, m, n, red, groups, us)
+
+
 @pytest.mark.parametrize("mode,m,n,red,groups", [
     (RAGGED_M, 1, 350080, 32, 1024),  # 1024 groups, one token: 3072 tile rows of 64, mostly of empty groups
     (RAGGED_M, 1000, 200064, 64, 2000),
