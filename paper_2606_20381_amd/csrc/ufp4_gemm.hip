@@ -742,6 +742,10 @@ constexpr GemmCost kGemmCost[kGemmKernels] = {
     {Direct32::BM, Direct32::BN, 3, 3.6, 1.8, 0.060, {0.024, 0.046, 0.063}},
     {Direct64::BM, Direct64::BN, 3, 6.0, 4.5, 0.188, {0.108, 0.129, 0.188}},
 };
+// The E2M1 128 x 64 kernel needs 81 registers, one more than three workgroups per CU leave (the uniform one 80): two, and
+// 155 instead of 127 cycles per 32 x 32 tile and block. us, 128 x 128 / 128 x 64 / 64 x 64: 368 x 16320 x 6528 192 / 211 /
+// 167, 10832 x 560 x 6720 179 / 215 / 171.
+constexpr GemmCost kCost128x64E2M1 = {Tile128x64::BM, Tile128x64::BN, 2, 5.0, 4.5, 0.258, {0.196, 0.360, 0.0}};
 
 // Ragged-M: every workgroup first finds its group (a prefix sum over the offsets and two barriers before any load), and
 // so do those that find none. Per workgroup and CU, measured on 2 to 256 groups. Without it, and with half a tile per group
@@ -755,7 +759,7 @@ static GemmKernel pick_kernel(const GemmJob& j) {
     GemmKernel best = kTile128;
     double best_us = 0.0;
     for (int k = 0; k < kGemmKernels; ++k) {
-        const GemmCost& c = kGemmCost[k];
+        const GemmCost& c = k == kTile128x64 && j.format == kFmtE2M1 ? kCost128x64E2M1 : kGemmCost[k];
         // launch limits: what the large tile's grid can hold must not fail on a smaller tile's (operands of millions of rows)
         const dim3 grid = gemm_grid(j, c.bm, c.bn);
         if (k != kTile128 && (grid.y > 65535u || grid.x >= 1u << 22)) continue;

@@ -55,6 +55,21 @@ def _assert_no_slower_than_the_large_tile(plan, mode, fmt, m, n, red, groups, us
     assert us[k] <= 1.04 * us[0], KERNELS[k]
 
 
+E2M1_TIMES = [  # mode, rows, columns, reduction, groups
+    (DENSE, 368, 16320, 6528, 1, (191.7, 205.4, 210.9, 221.7, 166.7)),
+    (DENSE, 10832, 560, 6720, 1, (178.9, 193.7, 215.4, 224.5, 171.0)),
+    (DENSE, 9296, 528, 1664, 1, (53.3, 60.0, 58.8, 57.8, 49.3)),
+    (RAGGED_M, 10206, 384, 1536, 8, (45.4, 56.1, 52.4, 45.9, 35.3)),
+    (RAGGED_M, 18958, 256, 1280, 32, (41.1, 49.2, 49.7, 52.5, 40.9)),
+]
+
+
+@pytest.mark.parametrize("mode,m,n,red,groups,us", E2M1_TIMES)
+def test_e2m1_kernels(plan, mode, m, n, red, groups, us):
+    """The E2M1 128 x 64 kernel runs two workgroups per CU, the uniform one three."""
+    _assert_no_slower_than_the_large_tile(plan, mode, U.E2M1, m, n, red, groups, us)
+
+
 @pytest.mark.parametrize("fmt,m,n,red,groups,us", RAGGED_M_TIMES)
 def test_ragged_m_kernels(plan, fmt, m, n, red, groups, us):
     _assert_no_slower_than_the_large_tile(plan, RAGGED_M, fmt, m, n, red, groups, us)
