@@ -724,7 +724,8 @@ static hipError_t launch_direct(const GemmJob& j, hipStream_t s) {
 //     fixed + (rounds - 1) * again + blocks * ((rounds - 1) * round + slope[workgroups per CU in the last round - 1])
 // with slope[n - 1] the time per K-block of n workgroups sharing a CU and `round` that of a full round followed by
 // others, whose start hides its end. Microseconds, measured on gfx950 (256 CUs) on
-// grids of 1/4 to 8 workgroups per CU at K = 512, 2048 and 4096. The large tile stages least per output (an asymptotic
+// grids of 1/4 to 8 workgroups per CU at K = 512, 2048 and 4096; the 32 x 32 row's `again` at K = 32 to 256, where a round
+// is little else (with 1.8, fitted at the longer ones: 240 x 5328 x 160 8.3 us on it, 5.7 on 128 x 64). The large tile stages least per output (an asymptotic
 // 111 cycles per 32 x 32 tile and block, against 127 for 128 x 64, 130 for the 64 x 64 and 186 for the 32 x 32 direct
 // tiles) but needs 512 tiles to fill the chip; smaller tiles and a split reduction give up some of that for a full chip
 // and a shorter chain per workgroup. Measured, us, 128 x 128 only -> picked: 256 x 512 x 256 8.7 -> 3.9, 64 x 4096 x
@@ -739,7 +740,7 @@ constexpr GemmCost kGemmCost[kGemmKernels] = {
     {Tile128::BM, Tile128::BN, 2, 5.0, 5.0, 0.405, {0.267, 0.442, 0.0}},
     {Tile128K2::BM, Tile128K2::BN, 1, 7.0, 5.0, 0.217, {0.217, 0.0, 0.0}},
     {Tile128x64::BM, Tile128x64::BN, 3, 5.0, 4.5, 0.345, {0.195, 0.245, 0.370}},
-    {Direct32::BM, Direct32::BN, 3, 3.6, 1.8, 0.060, {0.024, 0.046, 0.063}},
+    {Direct32::BM, Direct32::BN, 3, 3.6, 2.6, 0.060, {0.024, 0.046, 0.063}},
     {Direct64::BM, Direct64::BN, 3, 6.0, 4.5, 0.188, {0.108, 0.129, 0.188}},
 };
 // The E2M1 128 x 64 kernel needs 81 registers, one more than three workgroups per CU leave (the uniform one 80): two, and

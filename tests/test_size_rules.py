@@ -55,6 +55,21 @@ def _assert_no_slower_than_the_large_tile(plan, mode, fmt, m, n, red, groups, us
     assert us[k] <= 1.04 * us[0], KERNELS[k]
 
 
+SHORT_TIMES = [  # mode, format, rows, columns, reduction: few blocks, more than three 32 x 32 workgroups per CU
+    (DENSE, U.UNIFORM, 240, 5328, 160, (7.3, 8.4, 5.7, 8.3, 7.0)),
+    (DENSE, U.UNIFORM, 96, 12192, 128, (6.9, 7.9, 5.3, 7.3, 6.4)),
+    (DENSE, U.E2M1, 128, 11056, 192, (7.4, 8.1, 6.2, 8.4, 7.2)),
+    (DENSE, U.E2M1, 3488, 416, 128, (6.7, 8.2, 5.5, 8.0, 6.2)),
+    (RAGGED_K, U.UNIFORM, 512, 2688, 112, (7.0, 7.8, 5.9, 9.6, 7.0)),
+    (RAGGED_K, U.E2M1, 1792, 768, 128, (7.4, 8.7, 6.3, 9.7, 7.1)),
+]
+
+
+@pytest.mark.parametrize("mode,fmt,m,n,red,us", SHORT_TIMES)
+def test_short_reductions(plan, mode, fmt, m, n, red, us):
+    _assert_no_slower_than_the_large_tile(plan, mode, fmt, m, n, red, 1, us)
+
+
 E2M1_TIMES = [  # mode, rows, columns, reduction, groups
     (DENSE, 368, 16320, 6528, 1, (191.7, 205.4, 210.9, 221.7, 166.7)),
     (DENSE, 10832, 560, 6720, 1, (178.9, 193.7, 215.4, 224.5, 171.0)),
