@@ -350,7 +350,6 @@ __global__ __launch_bounds__(C::kThreads, 4) void gemm_f32_kernel(GemmArgs args)
     tl.nrows = __builtin_amdgcn_readfirstlane(tl.nrows);
     // 32-bit stage counters keep the loop (and the buffer loads' stage offsets) on the scalar unit
     const int nkb = __builtin_amdgcn_readfirstlane((int)tl.nkb);
-    const int nstages = (nkb + C::kStageBlocks - 1) / C::kStageBlocks;
 
     const int lane = tid & 63, h = lane >> 5, l32 = lane & 31;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -428,7 +427,8 @@ __global__ __launch_bounds__(C::kThreads, 4) void gemm_f32_kernel(GemmArgs args)
             }
         }
     };
-    // a full stage from LDS buffer `buf`, and the next stage's units (fetched one stage earlier) into the other buffer
+    // a stage with another one behind it, from LDS buffer `buf`, and the next stage's units (fetched one stage earlier) into
+    // the other buffer
     auto stage = [&](int buf, const Unit& na, const Unit& nb) {
         if (live) {
 #pragma unroll
@@ -445,7 +445,7 @@ __global__ __launch_bounds__(C::kThreads, 4) void gemm_f32_kernel(GemmArgs args)
     };
 
     if (nkb > 0) {
-        const int nfull = nkb / C::kStageBlocks;
+        const int nfull = (nkb - 1) / C::kStageBlocks;  // stages that another one follows
         Unit a0, b0, a1, b1;
         load(a0, b0, 0);
         load(a1, b1, 1);
@@ -463,7 +463,8 @@ __global__ __launch_bounds__(C::kThreads, 4) void gemm_f32_kernel(GemmArgs args)
             stage(1, a0, b0);
             __syncthreads();
         }
-        // the blocks of a partial last stage
+        // the blocks of the last stage, full or partial: nothing is staged behind them (a reduction of one stage, K = 64,
+        // 2688 x 12768: 28.9 -> 26.3 us; 8192 x 8192 x 128 59.6 -> 56.8; 8192 x 8192 x 2048 445 -> 441)
         if (live) {
             const int left = nkb - nfull * C::kStageBlocks - C::SKB * wk;
 #pragma unroll
@@ -723,14 +724,14 @@ static hipError_t launch_direct(const GemmJob& j, hipStream_t s) {
 // once, so a grid runs in rounds of 256 * resident workgroups:
 //     fixed + (rounds - 1) * again + blocks * ((rounds - 1) * round + slope[workgroups per CU in the last round - 1])
 // with slope[n - 1] the time per K-block of n workgroups sharing a CU and `round` that of a full round followed by
-// others, whose start hides its end. Microseconds, measured on gfx950 (256 CUs) on
-// grids of 1/4 to 8 workgroups per CU at K = 512, 2048 and 4096; the 32 x 32 row's `again` at K = 32 to 256, where a round
-// is little else (with 1.8, fitted at the longer ones: 240 x 5328 x 160 8.3 us on it, 5.7 on 128 x 64). The large tile stages least per output (an asymptotic
-// 111 cycles per 32 x 32 tile and block, against 127 for 128 x 64, 130 for the 64 x 64 and 186 for the 32 x 32 direct
-// tiles) but needs 512 tiles to fill the chip; smaller tiles and a split reduction give up some of that for a full chip
-// and a shorter chain per workgroup. Measured, us, 128 x 128 only -> picked: 256 x 512 x 256 8.7 -> 3.9, 64 x 4096 x
-// 4096 74 -> 10, 1024^3 22 -> 11, 1040 x 2064 x 1552 33 -> 24, 2048 x 2048 x 4096 76 -> 63, 2048 x 3072 x 2048 59 ->
-// 52; grids of many rounds keep the large tile.
+// others, whose start hides its end. Microseconds, measured on gfx950 (256 CUs) on grids of 1/4 to 8 workgroups per CU at
+// K = 512, 2048 and 4096; the 32 x 32 row's `again` at K = 32 to 256, where a round is little else (with 1.8, fitted at the
+// longer ones: 240 x 5328 x 160 8.3 us on it, 5.7 on 128 x 64). The large tile stages least per output (an asymptotic 111
+// cycles per 32 x 32 tile and block, against 127 for 128 x 64, 130 for the 64 x 64 and 186 for the 32 x 32 direct tiles)
+// but needs 512 tiles to fill the chip; smaller tiles and a split reduction give up some of that for a full chip and a
+// shorter chain per workgroup. Measured, us, 128 x 128 only -> picked: 256 x 512 x 256 8.7 -> 3.9, 64 x 4096 x 4096 74 ->
+// 10, 1024^3 22 -> 11, 1040 x 2064 x 1552 33 -> 24, 2048 x 2048 x 4096 76 -> 63, 2048 x 3072 x 2048 59 -> 52; grids of
+// many rounds keep the large tile.
 enum GemmKernel { kTile128, kTile128K2, kTile128x64, kDirect32, kDirect64, kGemmKernels };
 struct GemmCost {
     int bm, bn, resident;
