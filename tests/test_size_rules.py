@@ -145,3 +145,15 @@ def test_quantizer_tiles_where_they_are_faster(plan, fmt, rounding, dual, rht, r
     plan.ufp4_plan_tile_most.restype = ctypes.c_int64
     tiles = rows * cols <= plan.ufp4_plan_tile_most(fmt, rounding, dual, rht)
     assert tiles == (tile < register)
+
+
+@pytest.mark.parametrize("m,n,red,groups,a_rows,us", [  # us of the 256 x 256, 128 x 128 and 64 x 64 tiles
+    (12759, 512, 2432, 64, 16384, (34.9, 33.7, 38.9)), (2704, 1280, 256, 256, 33664, (91.3, 86.4, 98.2)),
+    (778, 2560, 896, 16, 2304, (18.5, 21.4, 19.6)), (3375, 2304, 512, 4, 3584, (15.4, 16.2, 16.2)),
+    (9273, 1792, 256, 16, 10496, (25.2, 23.1, 26.5)), (48961, 384, 256, 4, 49152, (23.3, 18.7, 24.3)),
+    (31445, 384, 1664, 8, 31872, (42.0, 29.6, 35.7)), (5267, 2688, 4096, 4, 5376, (86.0, 51.4, 83.2)),
+    (17081, 1408, 2560, 32, 19200, (93.0, 74.7, 101.8)), (601, 256, 384, 128, 16384, (12.1, 8.9, 11.0)),
+])
+def test_mx_ragged_m_tiles(plan, m, n, red, groups, a_rows, us):
+    tile, _ = mx_kernel(plan, RAGGED_M, m, n, red, groups, a_rows)
+    assert us[(256, 128, 64).index(tile)] <= 1.04 * us[0], tile
