@@ -750,10 +750,11 @@ constexpr GemmCost kGemmCost[kGemmKernels] = {
 constexpr GemmCost kCost128x64E2M1 = {Tile128x64::BM, Tile128x64::BN, 2, 5.0, 4.5, 0.258, {0.196, 0.360, 0.0}};
 
 // Ragged-M: every workgroup first finds its group (a prefix sum over the offsets and two barriers before any load), and
-// so do those that find none. Per workgroup and CU, measured on 2 to 256 groups. Without it, and with half a tile per group
-// counted, small tiles were taken for many small groups, us, 128 x 128 / then picked / now: 1273 tokens of 128 groups,
-// 5248 x 256 122 / 165 / 122; 600 of 256, 1536 x 256 66 / 96 / 66; one group of 3124, 1280 x 1152 35 / 44 / 28.
-constexpr double kLookupUs = 1.0;
+// so do those that find none. Per workgroup and CU: of 0.1 to 1 the value closest to the fastest kernel over 734 problems of
+// 1 to 256 groups (1.9% above it; 4.7% without it and with half a tile per group counted). us, 128 x 128 / then picked /
+// now: 1273 tokens of 128 groups, 5248 x 256 122 / 165 / 122; 600 of 256, 1536 x 256 66 / 96 / 66; one group of 3124,
+// 1280 x 1152 35 / 44 / 32.
+constexpr double kLookupUs = 0.75;
 
 static GemmKernel pick_kernel(const GemmJob& j) {
     constexpr double kCUs = 256.0;

@@ -403,10 +403,11 @@ constexpr MxCost kMxCost[kMxKernels] = {
     {MxTile64::BM, MxTile64::kThreads, 4, 3.5, 2.3, 0.62, {0.262, 0.326, 0.523, 0.647}},
 };
 
-// Ragged-M: every workgroup first finds its group, those that find none included. Per workgroup and CU, measured on 1 to 256
-// groups. Without it, and with half a tile per group counted, us, 256 x 256 / then picked / now: 12759 tokens of 64 groups,
-// 512 x 2432 35 / 38 / 35; 2704 of 256, 1280 x 256 91 / 97 / 86; 31445 of 8, 384 x 1664 42 / 42 / 30.
-constexpr double kMxLookupUs = 0.5;
+// Ragged-M: every workgroup first finds its group, those that find none included. Per workgroup and CU: of 0.1 to 1 the value
+// closest to the fastest tile over 366 problems of 1 to 256 groups (1.2% above it; 4.1% without it and with half a tile per
+// group counted). us, 256 x 256 / then picked / now: 12759 tokens of 64 groups, 512 x 2432 35 / 38 / 35; 31445 of 8, 384 x
+// 1664 42 / 42 / 30; 17081 of 32, 1408 x 2560 93 / 92 / 75.
+constexpr double kMxLookupUs = 0.25;
 
 static MxKernel pick_mx(const MxGemmJob& j) {
     constexpr double kCUs = 256.0;

@@ -148,7 +148,7 @@ def test_quantizer_tiles_where_they_are_faster(plan, fmt, rounding, dual, rht, r
 
 
 @pytest.mark.parametrize("m,n,red,groups,a_rows,us", [  # us of the 256 x 256, 128 x 128 and 64 x 64 tiles
-    (12759, 512, 2432, 64, 16384, (34.9, 33.7, 38.9)), (2704, 1280, 256, 256, 33664, (91.3, 86.4, 98.2)),
+    (12759, 512, 2432, 64, 16384, (34.9, 33.7, 38.9)), (683, 512, 896, 64, 8320, (17.3, 12.2, 15.1)),
     (778, 2560, 896, 16, 2304, (18.5, 21.4, 19.6)), (3375, 2304, 512, 4, 3584, (15.4, 16.2, 16.2)),
     (9273, 1792, 256, 16, 10496, (25.2, 23.1, 26.5)), (48961, 384, 256, 4, 49152, (23.3, 18.7, 24.3)),
     (31445, 384, 1664, 8, 31872, (42.0, 29.6, 35.7)), (5267, 2688, 4096, 4, 5376, (86.0, 51.4, 83.2)),
