@@ -1,10 +1,12 @@
 """GPU parity of the block-scaled GEMM at sizes that take each of its kernels (32 x 32 and 64 x 64 direct tiles, 128 x 128
-in one and two K groups, 128 x 64), with partial tiles on both axes, partial K stages and a padded output, against the
+in one and two K groups, 128 x 64; asserted through the library's size rule), with partial tiles on both axes, partial K stages and a padded output, against the
 oracle's fp64 product on sampled rows and columns around every tile edge.
 
 Tolerance: the kernels add fp32 products of exact block sums in fp32, one rounding of 2^-24 per block and at most
 K / 16 = 192 blocks here, so a relative Frobenius error below 192 * 2^-24 = 1.2e-5 in the worst case and about
 sqrt(192) * 2^-24 = 8e-7 for independent roundings; 2e-6 is asked for fp32 outputs and 2^-8 for bf16 ones."""
+
+import ctypes
 
 import numpy as np
 import pytest
@@ -14,18 +16,23 @@ from oracle import ufp4_oracle as O
 from paper_2606_20381_amd import ufp4 as U
 from paper_2606_20381_amd import workloads as WL
 from tests import parity as P
+from tests import test_size_rules as rules
 
 pytestmark = pytest.mark.gpu
 
-# (M, N, K): the kernel the size rule takes
+# (M, N, K), the kernel that the size rule takes, the formats for which it does
+BOTH = (O.UNIFORM, O.E2M1)
 SHAPES = [
-    (33, 65, 16),  # 32 x 32: a single block, one row and one column past a tile
-    (95, 64, 1552),  # 32 x 32: 97 blocks over eight waves in groups of four
-    (1040, 2064, 1552),  # 64 x 64
-    (130, 1100, 3072),  # 32 x 32, many rounds of groups
-    (1990, 2040, 2064),  # 128 x 128 in two K groups: 129 blocks in stages of eight
-    (2900, 2000, 1008),  # 128 x 64: 63 blocks in stages of four
-    (6000, 8200, 272),  # 128 x 128: 17 blocks in stages of four
+    ((33, 65, 16), "32x32", BOTH),  # a single block, one row and one column past a tile
+    ((95, 64, 1552), "32x32", BOTH),  # 97 blocks over eight waves in groups of four
+    ((1040, 2064, 1552), "64x64", BOTH),
+    ((130, 1100, 3072), "32x32", BOTH),  # many rounds of groups
+    ((1990, 2040, 2064), "128x128 in two K groups", BOTH),  # 129 blocks in stages of eight
+    ((2900, 2000, 1008), "128x64", (O.UNIFORM,)),  # 63 blocks in stages of four
+    ((2900, 2000, 1008), "128x128", (O.E2M1,)),
+    ((250, 5328, 160), "128x64", BOTH),  # ten blocks
+    ((6000, 8200, 272), "128x128", BOTH),  # 17 blocks in stages of four
+    ((2700, 12768, 64), "128x128", BOTH),  # one full stage
 ]
 
 
@@ -45,10 +52,11 @@ def _edges(n):
     return np.array(sorted(e))
 
 
-@pytest.mark.parametrize("mnk", SHAPES)
-@pytest.mark.parametrize("fmt", [O.UNIFORM, O.E2M1])
-def test_every_gemm_kernel(mnk, fmt):
+@pytest.mark.parametrize("mnk,kernel,fmt", [(s, kernel, f) for s, kernel, fmts in SHAPES for f in fmts])
+def test_every_gemm_kernel(mnk, kernel, fmt):
     m, n, k = mnk
+    plan = ctypes.CDLL(U.library_path())
+    assert rules.KERNELS[rules.gemm_kernel(plan, rules.DENSE, fmt, m, n, k)] == kernel
     g = torch.Generator().manual_seed(m + 3 * n + 7 * k + fmt)
     x = torch.randn(m, k, generator=g).bfloat16()
     w = (torch.randn(n, k, generator=g) * 0.02).bfloat16()
@@ -72,15 +80,16 @@ def test_every_gemm_kernel(mnk, fmt):
 @pytest.mark.parametrize("counts", [[1] * 40, [33, 0, 65, 200, 1, 31], [700, 3, 400]])
 def test_grouped_against_dense_per_group(counts):
     """Few tokens per group (small tiles): every group's rows equal the dense product of that group's rows up to the
-    order of the fp32 sums (both within 2e-6 of the exact product), and rows past the tokens stay unwritten."""
+    order of the fp32 sums (both within 2e-6 of the exact product), and rows past the last offset stay unwritten."""
     g = torch.Generator().manual_seed(sum(counts))
     E, N, K = len(counts), 144, 528
-    x = torch.randn(sum(counts), K, generator=g).bfloat16().cuda()
+    x = torch.randn(sum(counts) + 3, K, generator=g).bfloat16().cuda()  # three rows past the last offset
     w = (torch.randn(E * N, K, generator=g) * 0.02).bfloat16().cuda()
     off, _ = U.group_offsets(counts)
     xq, wq = U.rht_quantize(x, sign_mask=0x77), U.rht_quantize(w, sign_mask=0x77)
-    y = U.gemm_fwd_y_grouped(xq, wq, off)
+    y = U.gemm_fwd_y_grouped(xq, wq, off, out=torch.full((sum(counts) + 3, N), 7.0, device="cuda"))
     torch.cuda.synchronize()
+    assert bool((y[sum(counts):] == 7.0).all())
     at = 0
     for e, c in enumerate(counts):
         if c:

@@ -1,9 +1,12 @@
-"""GPU parity of the power-of-two-scale GEMM at sizes that take each of its tiles (64, 128, 256), with partial tiles on
+"""GPU parity of the power-of-two-scale GEMM at sizes that take each of its tiles (64, 128, 256; asserted through the
+library's size rule), with partial tiles on
 both axes, partial K stages and a padded output, against the oracle's fp64 product on sampled rows and columns around
 every tile edge.
 
 Tolerance: levels are integers times powers of two, the matrix core adds 64 products per instruction in fp32, so at most
 K / 64 = 32 roundings of 2^-24 here: below 2e-6 relative for fp32 outputs; bf16 outputs round once more (2^-9, 2^-8 asked)."""
+
+import ctypes
 
 import numpy as np
 import pytest
@@ -13,15 +16,18 @@ from oracle import ufp4_oracle as O
 from paper_2606_20381_amd import ufp4 as U
 from paper_2606_20381_amd import workloads as WL
 from tests import parity as P
+from tests import test_size_rules as rules
 
 pytestmark = pytest.mark.gpu
 
-# (M, N, K): the tile the size rule takes
+# (M, N, K) and the tile that the size rule takes
 SHAPES = [
-    (33, 65, 32),  # 64: one block, one row and one column past a tile
-    (200, 136, 1056),  # 64: 33 blocks in stages of four
-    (2000, 2040, 2080),  # 128: 65 blocks
-    (4000, 4100, 352),  # 256: 11 blocks
+    ((33, 65, 32), 64),  # one block, one row and one column past a tile
+    ((200, 136, 1056), 64),  # 33 blocks in stages of four
+    ((4000, 4100, 352), 64),  # 11 blocks, more workgroups than one round
+    ((2000, 2040, 2080), 128),  # 65 blocks
+    ((3900, 4000, 672), 256),  # 21 blocks, partial tiles on both axes
+    ((8100, 8190, 96), 256),  # a single partial stage
 ]
 
 
@@ -41,9 +47,10 @@ def _edges(n):
     return np.array(sorted(e))
 
 
-@pytest.mark.parametrize("mnk", SHAPES)
-def test_every_mx_tile(mnk):
+@pytest.mark.parametrize("mnk,tile", SHAPES)
+def test_every_mx_tile(mnk, tile):
     m, n, k = mnk
+    assert rules.mx_kernel(ctypes.CDLL(U.library_path()), rules.DENSE, m, n, k)[0] == tile
     g = torch.Generator().manual_seed(m + 3 * n + 7 * k)
     x = torch.randn(m, k, generator=g).bfloat16()
     w = (torch.randn(n, k, generator=g) * 0.02).bfloat16()

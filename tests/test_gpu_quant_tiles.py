@@ -54,14 +54,15 @@ def test_transposed_tiles(shape, fmt, rounding):
     fn(xd[:, :cols], transpose=True, rht=True, sign_mask=0x1234, rounding=rounding, seed=9, stream_id=1, out=q)
     torch.cuda.synchronize()
     bits = WL.bf16_bits(x.contiguous())
-    keep = slice(None) if rows < 10000 else slice(rows - 4096, rows)  # the last blocks of the long tensor
     if rows < 10000:
         idx, sc = P.oracle_operand(bits, "cols", fmt, rounding, True, 0x1234, 9, 1)
         P.assert_codes_equal(*P.gpu_rows(q), idx, sc, fmt, f"{shape}")
-    elif rounding == O.RTNE:  # RTNE does not number its blocks: a slice of the reduction stands alone
-        idx, sc = P.oracle_operand(bits[keep], "cols", fmt, rounding, True, 0x1234, 9, 1)
+    else:  # more blocks than one row of the grid: the last 256, at their block numbers (the draws count them)
+        blk0 = rows // 16 - 256
+        a = np.ascontiguousarray(O.bf16_bits_to_f32(bits[16 * blk0:]).T)
+        idx, sc = O.quantize_rows(a, fmt, rounding, True, 0x1234, 9, 1, block_base=blk0)
         codes, scales = P.gpu_rows(q)
-        P.assert_codes_equal(codes[:, -4096 // 2:], scales[:, -4096 // 16:], idx, sc, fmt, f"{shape}")
+        P.assert_codes_equal(codes[:, 8 * blk0:], scales[:, blk0:], idx, sc, fmt, f"{shape}")
     assert _padding_is_zero(q)
 
 
