@@ -421,6 +421,10 @@ int ufp4_mx_gemm_bwd_dw_grouped(const ufp4_qtensor *dyt, const ufp4_qtensor *xt,
  * Both operands must be UFP4_FMT_UNIFORM or both UFP4_FMT_E2M1 with the same rht_block, sign words and
  * reduction length, else UFP4_ERR_MISMATCH. out_dtype UFP4_OUT_F32 or UFP4_OUT_BF16; out_dev row-major with
  * leading dimension ldc (elements).
+ *
+ * One problem gives the same bits on every call. The kernel is chosen by the problem's size, and the kernels add a
+ * reduction's blocks in different orders: an output's last fp32 bits may differ between a row computed by itself, within a
+ * larger batch and within a group (here and in the grouped forms, and likewise for the power-of-two-scale GEMMs above).
  */
 int ufp4_gemm_fwd_y(const ufp4_qtensor *x, const ufp4_qtensor *w, void *y_dev, int64_t ldc, int out_dtype,
                     void *stream);
@@ -443,8 +447,8 @@ int ufp4_gemm_bwd_dw(const ufp4_qtensor *dyt, const ufp4_qtensor *xt, void *dw_d
  *           ufp4_quantize_grouped_t on the same offsets; the padded offsets pad_g are computed on the device.
  *
  * Offsets are read on the device: rows past M_total and reduction positions past R are ignored, output rows
- * past off_G (fwd_y, bwd_dx) are not written, groups with no tokens give dW_g = 0. Operand checks as for the dense calls; besides, fwd_y takes plain operands, bwd_dx a
- * plain Qdy and a plain or grouped-transposed Qwt (the same bytes: N is a multiple of 16), bwd_dw two
+ * past off_G (fwd_y, bwd_dx) are not written, groups with no tokens give dW_g = 0. Operand checks as for the dense
+ * calls; besides, fwd_y takes plain operands, bwd_dx a plain Qdy and a plain or grouped-transposed Qwt (the same bytes: N is a multiple of 16), bwd_dw two
  * grouped-transposed operands (UFP4_LAYOUT_GROUPED_RED); other forms return UFP4_ERR_MISMATCH. num_groups up to
  * 65535.
  */

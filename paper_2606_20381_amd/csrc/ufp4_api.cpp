@@ -225,7 +225,8 @@ int mx_gemm_impl(const ufp4_qtensor* a, const ufp4_qtensor* b, void* c, int64_t 
     if (a->red != b->red) return UFP4_ERR_MISMATCH;
     st = check_output(c, ldc, b->rows, out_dtype, a->rows == 0 || b->rows == 0);
     if (st != UFP4_OK) return st;
-    // one workgroup per 256 x 256 output tile on a one-dimensional grid (the count of 128 x 128 tiles bounds it)
+    // one workgroup per output tile on a one-dimensional grid (bounded by the count of 128 x 128 tiles; smaller ones are
+    // taken only where their own grid fits)
     if (ceil_div(a->rows, 128) * ceil_div(b->rows, 128) >= (int64_t(1) << 31)) return UFP4_ERR_UNSUPPORTED;
     if (a->rows == 0 || b->rows == 0) return UFP4_OK;
     MxGemmJob j{};
@@ -539,7 +540,7 @@ int ufp4_quantize_dual(int format, const void* x_dev, int64_t rows, int64_t cols
                                 rows);
     if (st != UFP4_OK) return st;
     if (out_rows == out_cols) return UFP4_ERR_INVALID_ARG;
-    // grid: x over 64-column tiles of the padded columns, y over 32 groups of 16 rows (grid-stride beyond)
+    // grid: x over tiles of at least 64 padded columns, y over groups of rows (grid-stride beyond)
     if (padded_rows(cols) / 64 >= (int64_t(1) << 31)) return UFP4_ERR_UNSUPPORTED;
     const uint16_t mr = (uint16_t)sign_mask_rows, mc = (uint16_t)sign_mask_cols;
     record(out_rows, format, rows, cols, rht_rows ? 16 : 0, &mr, 0.0f, rounding);
@@ -678,7 +679,7 @@ int ufp4_mx_quantize_grouped(const void* x_dev, int64_t rows, int64_t cols, int6
     if (st != UFP4_OK) return st;
     if (qrows >= (int64_t(1) << 31) || red / 16 >= (int64_t(1) << 31)) return UFP4_ERR_UNSUPPORTED;
     if (!transpose && padded_rows(qrows) / 64 > 65535) return UFP4_ERR_UNSUPPORTED;
-    // grid y: chunks of four 256-column tiles of X (its padded columns for the transposed form)
+    // at most 65535 chunks of 1024 columns of X (its padded columns for the transposed form)
     if (((transpose ? padded_rows(cols) : cols) + 1023) / 1024 > 65535) return UFP4_ERR_UNSUPPORTED;
     const uint16_t mask16 = (uint16_t)sign_mask;
     record(out, UFP4_FMT_UNIFORM_MX32, qrows, red, rht ? 16 : 0, &mask16, 0.0f, rounding,

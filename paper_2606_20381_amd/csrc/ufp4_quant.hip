@@ -13,15 +13,14 @@
 // 4 amax, RN32(g / amax') = r / 4, y' * RN32(g / amax') = y * r exactly, and s = RN32(amax' / g) / 4. For bf16
 // inputs y' = 4y holds for every output (a sum below 2^-124 is a multiple of 2^-133 with at most 9 significant
 // bits, so both it and a quarter of it are exact fp32 numbers); with amax' in [2^-121, 2^127) (or 0) the
-// quotients are normal and these identities are exact (s by the FMA-corrected product, r by an IEEE division). Any other block takes the exact path (`quant_core`),
-// which rescales the block by a power of two before the reciprocal. Real data never leaves the fast range; the
-// check costs three instructions per block.
+// quotients are normal and these identities are exact (s by the FMA-corrected product, r by an IEEE division). Any
+// other block takes the exact path (`quant_core`), which rescales the block by a power of two before the reciprocal.
+// Real data never leaves the fast range; the check costs three instructions per block.
 //
-// Two input layouts: rowwise (reduction axis contiguous, one thread per block, 32-byte loads) and
-// transposed (reduction axis strided: each thread loads a 16-row x 8-column sub-tile and builds its eight
-// column blocks in registers). The transposed kernel also serves grouped (MoE) tensors whose token axis is
-// cut into groups that are zero-padded to a multiple of 16. A third kernel produces both operands of one
-// tensor (rowwise and transposed) from a single read of it.
+// Layouts: rowwise (reduction axis contiguous, one thread per block, 32-byte loads); transposed (reduction axis strided),
+// by 16 x 256 tiles through LDS with one block per thread, or for large tensors by 16 x 8 sub-tiles in a thread's registers
+// (kColsTileMost); both operands of one tensor from a single read, the same two ways (kDualTileMost); grouped (MoE)
+// transposed tensors, whose token axis is cut into groups zero-padded to a multiple of 16, on the tiles.
 //
 // Output layout (panels): the quantized operand's rows are cut into panels of 128; within a panel, block b
 // of all 128 rows is stored contiguously (codes: 128 x 8 bytes at b * 1024; scales: 128 floats at b * 128).
@@ -575,10 +574,11 @@ constexpr int kXG = 64 / kXC;  // block-n RHT
 constexpr int kXGD = 32;       // otherwise
 static_assert(kXC == 8 || kXC == 4, "columns per thread");
 
-// The uniform grid is bounded to three waves per SIMD (SR: 178 -> 172 us on 16384^2); E2M1 would spill.
+// The uniform grid is bounded to three waves per SIMD (SR with the rotation: 178 -> 172 us on 16384^2); E2M1 has three
+// without a bound.
 template <int FMT, int ROUND, bool RHT, bool WIDE = false>
 __global__ __launch_bounds__(256, FMT == kFmtUniform && !WIDE ? 3 : 1) void quant_cols_kernel(
-    const uint16_t* __restrict__ x, int64_t rows, int64_t cols, int64_t prows, int64_t ld, int64_t red_total, QuantArgs qa,
+    const uint16_t* __restrict__ x, int64_t cols, int64_t prows, int64_t ld, int64_t nblk, QuantArgs qa,
     uint8_t* __restrict__ codes, int64_t code_pld, float* __restrict__ scales, int64_t scale_pld) {
     const int t = threadIdx.x;
     constexpr int XG = WIDE ? kXG : kXGD, XB = 256 / XG;  // column groups, blocks per workgroup
@@ -594,33 +594,22 @@ __global__ __launch_bounds__(256, FMT == kFmtUniform && !WIDE ? 3 : 1) void quan
     // its slot of the stage, and stores to panels past the end are skipped.
     if (!STAGE && cbase >= prows) return;
     const int ncol = cols - cbase < kXC ? (int)(cols - cbase) : kXC;  // valid columns of the thread (<= 0: none)
-    const int64_t nblk = red_total / kBlock;
     constexpr int kW = kXC / 2;  // dwords per row
 
     for (int64_t gb = (int64_t)blockIdx.y * XB + rb; gb < nblk; gb += (int64_t)gridDim.y * XB) {
-        const int64_t src0 = gb * kBlock;
-        int64_t nvalid = kBlock;
-        if (src0 + nvalid > rows) nvalid = rows - src0;
-
         uint32_t v[kBlock][kW];
-        if (ncol == kXC && nvalid == kBlock) {  // the common case: a full 16 x kXC sub-tile, no per-row tests
+        if (ncol == kXC) {  // the common case: a full 16 x kXC sub-tile
 #pragma unroll
-            for (int j = 0; j < kBlock; ++j) load_row_chunk<kXC>(x + (src0 + j) * ld + cbase, v[j]);
-        } else {
+            for (int j = 0; j < kBlock; ++j) load_row_chunk<kXC>(x + (gb * kBlock + j) * ld + cbase, v[j]);
+        } else {  // ragged last columns: no read past column cols - 1
 #pragma unroll
             for (int j = 0; j < kBlock; ++j) {
+                const uint16_t* src = x + (gb * kBlock + j) * ld + cbase;
 #pragma unroll
                 for (int k = 0; k < kW; ++k) v[j][k] = 0;
-                if (j < nvalid) {
-                    const uint16_t* src = x + (src0 + j) * ld + cbase;
-                    if (ncol == kXC) {
-                        load_row_chunk<kXC>(src, v[j]);
-                    } else if (ncol > 0) {  // ragged last columns: no read past column cols - 1
 #pragma unroll
-                        for (int k = 0; k < kXC; ++k)
-                            if (k < ncol) v[j][k >> 1] |= (uint32_t)src[k] << (16 * (k & 1));
-                    }
-                }
+                for (int k = 0; k < kXC; ++k)
+                    if (k < ncol) v[j][k >> 1] |= (uint32_t)src[k] << (16 * (k & 1));
             }
         }
         // Columns past `cols` hold zeros: such a block quantizes to zero codes and a +0 scale, the padding value, so
@@ -1442,10 +1431,11 @@ template <int FMT, int ROUND, bool RHT, bool WIDE>
 static hipError_t launch_cols_regs(const QuantJob& j, hipStream_t s) {
     constexpr int XG = WIDE ? kXG : kXGD, XB = 256 / XG;
     const int64_t prows = padded_rows(j.qrows);
-    const dim3 grid((unsigned)((prows + XG * kXC - 1) / (XG * kXC)), grid_y((j.red / kBlock + XB - 1) / XB));
+    const int64_t nblk = j.red / kBlock;  // whole blocks: the reduction is X's rows
+    const dim3 grid((unsigned)((prows + XG * kXC - 1) / (XG * kXC)), grid_y((nblk + XB - 1) / XB));
     quant_cols_kernel<FMT, ROUND, RHT, WIDE><<<grid, 256, 0, s>>>(
-        static_cast<const uint16_t*>(j.x), j.xrows, j.qrows, prows, j.ld, j.red, j.qa, static_cast<uint8_t*>(j.codes),
-        j.code_pld, j.scales, j.scale_pld);
+        static_cast<const uint16_t*>(j.x), j.qrows, prows, j.ld, nblk, j.qa, static_cast<uint8_t*>(j.codes), j.code_pld,
+        j.scales, j.scale_pld);
     return hipGetLastError();
 }
 
