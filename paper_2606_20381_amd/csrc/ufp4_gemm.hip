@@ -816,3 +816,29 @@ extern "C" int ufp4_plan_gemm(int mode, int format, int64_t M, int64_t N, int64_
     j.G = G;
     return ufp4::pick_kernel(j);
 }
+
+namespace ufp4 {
+template <int FMT, int OUT>
+static int gemm_resident(int kernel) {
+    int n = 0;
+    hipError_t e = hipErrorInvalidValue;
+    switch (kernel) {
+        case kTile128: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, gemm_f32_kernel<FMT, OUT, Tile128>, Tile128::kThreads, 0); break;
+        case kTile128K2: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, gemm_f32_kernel<FMT, OUT, Tile128K2>, Tile128K2::kThreads, 0); break;
+        case kTile128x64: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, gemm_f32_kernel<FMT, OUT, Tile128x64>, Tile128x64::kThreads, 0); break;
+        case kDirect32: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, gemm_direct_kernel<FMT, OUT, Direct32>, Direct32::kThreads, 0); break;
+        case kDirect64: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, gemm_direct_kernel<FMT, OUT, Direct64>, Direct64::kThreads, 0); break;
+        default: break;
+    }
+    return e == hipSuccess ? n : -1;
+}
+}  // namespace ufp4
+
+extern "C" int ufp4_plan_gemm_resident(int kernel, int format, int out_dtype, int* costed) {
+    using namespace ufp4;
+    if (kernel < 0 || kernel >= kGemmKernels) return -1;
+    const bool e2m1 = format == kFmtE2M1, bf16 = out_dtype == kOutBF16;
+    *costed = (kernel == kTile128x64 && e2m1 ? kCost128x64E2M1 : kGemmCost[kernel]).resident;
+    if (e2m1) return bf16 ? gemm_resident<kFmtE2M1, kOutBF16>(kernel) : gemm_resident<kFmtE2M1, kOutF32>(kernel);
+    return bf16 ? gemm_resident<kFmtUniform, kOutBF16>(kernel) : gemm_resident<kFmtUniform, kOutF32>(kernel);
+}

@@ -465,3 +465,25 @@ extern "C" int ufp4_plan_gemm_mx(int mode, int64_t M, int64_t N, int64_t red, in
     *threads_x = mx_grid_tiles(j, kMxCost[k].tile) * kMxCost[k].threads;
     return k;
 }
+
+namespace ufp4 {
+template <int OUT>
+static int mx_resident(int kernel) {
+    int n = 0;
+    hipError_t e = hipErrorInvalidValue;
+    switch (kernel) {
+        case kMxTile256: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, gemm_mx_kernel<OUT, MxTile256>, MxTile256::kThreads, 0); break;
+        case kMxTile128: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, gemm_mx_kernel<OUT, MxTile128>, MxTile128::kThreads, 0); break;
+        case kMxTile64: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, gemm_mx_kernel<OUT, MxTile64>, MxTile64::kThreads, 0); break;
+        default: break;
+    }
+    return e == hipSuccess ? n : -1;
+}
+}  // namespace ufp4
+
+extern "C" int ufp4_plan_gemm_mx_resident(int kernel, int out_dtype, int* costed) {
+    using namespace ufp4;
+    if (kernel < 0 || kernel >= kMxKernels) return -1;
+    *costed = kMxCost[kernel].resident;
+    return out_dtype == kOutBF16 ? mx_resident<kOutBF16>(kernel) : mx_resident<kOutF32>(kernel);
+}

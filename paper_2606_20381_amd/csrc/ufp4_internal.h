@@ -201,7 +201,7 @@ hipError_t launch_gemm(const GemmJob& job, hipStream_t stream);
 
 }  // namespace ufp4
 
-// The size rules asked from the host, without a GPU: exported for the tests, not part of the interface in include/ufp4.h.
+// The size rules asked from the host: exported for the tests, not part of the interface in include/ufp4.h.
 // They return the kernel that a problem gets, as the enum of its rule.
 extern "C" {
 // `mode` a GemmMode; `red` the reduction (ragged-K: its padded total); `a_rows` the rows stored in A; *threads_x the
@@ -214,4 +214,8 @@ int64_t ufp4_plan_cols_wide(int rht_block, int64_t cols);
 int64_t ufp4_plan_grouped(int mx, int64_t tiles, int64_t* longest_run);
 // Elements up to which the tile kernel takes a transposed operand (dual: two operands; rht then: both rotated).
 int64_t ufp4_plan_tile_most(int format, int rounding, int dual, int rht);
+// On a GPU: how many workgroups of a kernel share a CU (-1 on an error), and how many its rule counts on.
+int ufp4_plan_gemm_resident(int kernel, int format, int out_dtype, int* costed);
+int ufp4_plan_gemm_mx_resident(int kernel, int out_dtype, int* costed);
+int ufp4_plan_grouped_resident(int mx, int rows, int format, int rounding, int* costed);
 }

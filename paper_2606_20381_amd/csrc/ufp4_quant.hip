@@ -1809,3 +1809,26 @@ extern "C" int64_t ufp4_plan_tile_most(int format, int rounding, int dual, int r
     if (format == kFmtE2M1) return rounding == kRoundSR ? tile_most<kFmtE2M1, kRoundSR>(dual, rht) : tile_most<kFmtE2M1, kRoundRTNE>(dual, rht);
     return rounding == kRoundSR ? tile_most<kFmtUniform, kRoundSR>(dual, rht) : tile_most<kFmtUniform, kRoundRTNE>(dual, rht);
 }
+
+namespace ufp4 {
+template <int FMT, int ROUND, bool RHT>
+static int grouped_resident() {
+    int n = 0;
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, quant_tile_grouped_kernel<FMT, ROUND, RHT>, 256, 0) == hipSuccess ? n : -1;
+}
+template <int ROUND, bool RHT, bool GROWS>
+static int mx_grouped_resident() {
+    int n = 0;
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, mx_tile_grouped_kernel<ROUND, RHT, GROWS>, 256, 0) == hipSuccess ? n : -1;
+}
+}  // namespace ufp4
+
+extern "C" int ufp4_plan_grouped_resident(int mx, int rows, int format, int rounding, int* costed) {
+    using namespace ufp4;  // the kernels with the rotation, which need the most registers
+    *costed = (int)(mx ? kMxGroupedResident : kGroupedResident);
+    const bool sr = rounding == kRoundSR;
+    if (mx && rows) return sr ? mx_grouped_resident<kRoundSR, true, true>() : mx_grouped_resident<kRoundRTNE, true, true>();
+    if (mx) return sr ? mx_grouped_resident<kRoundSR, true, false>() : mx_grouped_resident<kRoundRTNE, true, false>();
+    if (format == kFmtE2M1) return sr ? grouped_resident<kFmtE2M1, kRoundSR, true>() : grouped_resident<kFmtE2M1, kRoundRTNE, true>();
+    return sr ? grouped_resident<kFmtUniform, kRoundSR, true>() : grouped_resident<kFmtUniform, kRoundRTNE, true>();
+}

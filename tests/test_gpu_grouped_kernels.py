@@ -210,3 +210,22 @@ def test_mx_ragged_reduction(plan, tile, scale, n, k):
         return O.gemm_nt_mx(ia[:, s], ea[:, b], ib[:, s], eb[:, b])
 
     _check_dw(dw, counts, product)
+
+
+def test_workgroups_per_cu_are_what_the_rules_count_on(plan):
+    """A register more than a kernel's bound leaves fewer workgroups per CU than its cost row assumes."""
+    costed = ctypes.c_int()
+    for fmt in (O.UNIFORM, O.E2M1):
+        for out in (0, 1):
+            for k, name in enumerate(rules.KERNELS):
+                n = plan.ufp4_plan_gemm_resident(k, fmt, out, ctypes.byref(costed))
+                assert n == costed.value, (name, fmt, out, n)
+        for rounding in (O.RTNE, O.SR):
+            n = plan.ufp4_plan_grouped_resident(0, 0, fmt, rounding, ctypes.byref(costed))
+            assert n == costed.value, (fmt, rounding, n)
+    for k in range(3):
+        for out in (0, 1):
+            assert plan.ufp4_plan_gemm_mx_resident(k, out, ctypes.byref(costed)) == costed.value, (k, out)
+    for rows in (0, 1):
+        for rounding in (O.RTNE, O.SR):
+            assert plan.ufp4_plan_grouped_resident(1, rows, 0, rounding, ctypes.byref(costed)) == costed.value
