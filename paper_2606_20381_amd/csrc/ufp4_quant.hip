@@ -1371,7 +1371,9 @@ hipError_t launch_rht(const RhtJob& j, hipStream_t s) {
 //   E2M1 RTNE plain                     8192 x 11008 55 / 57   8192 x 13056 66 / 65   16384^2 155 / 138
 //   E2M1 SR, rotated                    16384^2 389 / 396, 32768 x 16384 746 / 785
 //   E2M1 SR plain                       24048 x 4624 147 / 148 16384 x 8192 168 / 168 16384^2 333 / 321
-//   two operands, uniform RTNE, both rotated 8192 x 9216 65 / 67, 8192 x 11008 79 / 76, 16384^2 227 / 208; one rotated
+//   two operands, uniform RTNE, both rotated 8192 x 9216 65 / 67, 8192 x 11008 79 / 76, 16384 x 8192 116 / 107, 16384^2
+//   227 / 208; from 80 Mi elements on alone and behind GEMMs that lower the clock tiles are 5-10% slower, in a layer step of
+//   160 tokens, of which the quantizer is a fifth, 5-7% faster (16224 x 5520 87 / 93, 8192 x 11008 88 / 94); one rotated
 //   16384 x 12288 144 / 150, 16384^2 188 / 187; uniform SR 12288^2 175 / 177, 16384 x 12288 232 / 231, 16384^2 309 / 299;
 //   E2M1 RTNE 12288^2 191 / 194, 16384 x 12288 254 / 253, 16384^2 336 / 332; E2M1 SR 16384^2 715 / 780.
 constexpr int64_t kMi = 1 << 20, kNoLimit = INT64_MAX;
@@ -1379,7 +1381,7 @@ template <int FMT, int ROUND, bool RHT>
 constexpr int64_t kColsTileMost = FMT == kFmtUniform ? (ROUND == kRoundRTNE ? (RHT ? 100 * kMi : kNoLimit) : (RHT ? 40 : 100) * kMi)
                                                      : (ROUND == kRoundRTNE ? (RHT ? 64 : 100) * kMi : (RHT ? kNoLimit : 128 * kMi));
 template <int FMT, int ROUND, bool BOTH>  // BOTH: both operands rotated
-constexpr int64_t kDualTileMost = FMT == kFmtUniform ? (ROUND == kRoundRTNE ? (BOTH ? 80 : 200) : (BOTH ? 160 : 200)) * kMi
+constexpr int64_t kDualTileMost = FMT == kFmtUniform ? (ROUND == kRoundRTNE ? (BOTH ? 100 : 200) : (BOTH ? 160 : 200)) * kMi
                                                      : (ROUND == kRoundRTNE ? 160 * kMi : kNoLimit);
 
 // Workgroups of the grouped kernels. Each scans the group offsets (up to 1025 of them, two barriers) before its run of
